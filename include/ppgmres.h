@@ -249,6 +249,26 @@ pp_status pp_matrix_march(pp_matrix A, int prec, int *steps, int *cz, double *us
 pp_status pp_matrix_set_march_shape(pp_matrix A, int prec, int shape);
 pp_status pp_matrix_march_shape(pp_matrix A, int prec, int *shape);
 
+/* Many chain steps per launch on a 2-D grid: when the matrix is a 5-point
+ * stencil on a gx x gy grid (constant or varying coefficients) or a 13-point
+ * one with constant coefficients (diagonals 0, +-1, +-2, +-gx, +-gx +-1,
+ * +-2 gx), a workgroup holds a region of 64 vx x waves ry points in
+ * registers (vx columns a lane, ry rows a wave), advances it by up to
+ * `steps` steps and stores the tile that is still exact: the region less
+ * one (13 points: two) points a step on each side where it does not end with
+ * the grid. p chains' accumulators are read and written once per launch. The
+ * results equal single launches up to the order of rounding. pp_matrix_tune
+ * times the likeliest shapes and keeps the fastest when it beats the others.
+ *   pp_matrix_set_grid: forces a shape (steps 2..32; 0 turns it off);
+ *     PP_EINVAL where it does not apply, for a shape that is not built or
+ *     whose region leaves no tile, for bfloat16 vectors, or for a precision
+ *     not tuned or set yet. pp_matrix_set_variant and the other fusion
+ *     controls turn it off.
+ *   pp_matrix_grid: shape (host int[4]) = {vx, ry, waves, steps} in use
+ *     (steps 0: off), us the tuned time of one launch (0: forced). */
+pp_status pp_matrix_set_grid(pp_matrix A, int prec, int vx, int ry, int waves, int steps);
+pp_status pp_matrix_grid(pp_matrix A, int prec, int *shape, double *us);
+
 /* Composition with a diagonal right preconditioner M^{-1} = diag(s)
  * (eqs. (1.3)-(1.4), section 1): from now on the handle's operator is
  * A diag(s). Its chains, pp_gmres_setup (the polynomial is built for

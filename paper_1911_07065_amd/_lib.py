@@ -60,6 +60,8 @@ SIGNATURES = {
     "pp_solve_workspace_bytes": (c_int, [c_void_p, c_void_p, ctypes.POINTER(SolveOpts), ctypes.POINTER(c_int64),
                                          ctypes.POINTER(c_int64)]),
     "pp_matrix_march_shape": (c_int, [c_void_p, c_int, P_int]),
+    "pp_matrix_set_grid": (c_int, [c_void_p, c_int, c_int, c_int, c_int, c_int]),
+    "pp_matrix_grid": (c_int, [c_void_p, c_int, P_int, P_double]),
     "pp_matrix_right_scale": (c_int, [c_void_p, c_void_p, c_void_p]),
     "pp_matrix_scale": (c_int, [c_void_p, c_void_p, c_void_p]),
     "pp_chain_variant_name": (ctypes.c_char_p, [c_int]),

@@ -182,6 +182,18 @@ class Matrix:
         check(lib.pp_matrix_march_shape(self.handle, PREC[prec], ctypes.byref(v)), "pp_matrix_march_shape")
         return v.value
 
+    def set_grid(self, prec: str, vx: int, ry: int, waves: int, steps: int):
+        """Up to `steps` (2..32) chain steps per launch on a 2-D grid stencil,
+        regions of 64 vx x waves ry points (steps 0: off)."""
+        check(lib.pp_matrix_set_grid(self.handle, PREC[prec], int(vx), int(ry), int(waves), int(steps)),
+              "pp_matrix_set_grid")
+
+    def grid(self, prec: str = "fp32"):
+        """((vx, ry, waves, steps), tuned us per launch) of the 2-D multi-step kernel (steps 0: off)."""
+        sh, us = (ctypes.c_int * 4)(), ctypes.c_double()
+        check(lib.pp_matrix_grid(self.handle, PREC[prec], sh, ctypes.byref(us)), "pp_matrix_grid")
+        return tuple(sh), us.value
+
     def constant_stencil(self) -> bool:
         """True when every row is one interior row's box stencil truncated at the box."""
         g, c = ctypes.c_int(), ctypes.c_int()

@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "../../include/ppgmres.h"
+#include "grid2.h"
 #include "host_core.h"
 #include "kernels.h"
 #include "poly.h"
@@ -106,6 +107,32 @@ struct pp_matrix_s {
     // run the whole-line tile kernel instead of the cube-tile pair kernel
     int pair_tile[3] = {0, 0, 0};
     int pair_remap[3] = {1, 1, 1};
+    // 2-D grid of a 5- or 13-point stencil matrix (g2_nd == 0: none; the
+    // diagonal format holds its values), the interior row's pattern when the
+    // coefficients are constant (-1: they are not, or no pattern copy) and,
+    // per precision, the shape of the multi-step kernel (steps 0: off) and
+    // the tuned time of one launch of it
+    int g2_nd = 0, g2_gx = 0, g2_gy = 0, g2_pint = -1;
+    Grid2Shape g2[3];
+    double g2_us[3] = {0, 0, 0};
+    Grid2Mat grid2() const {
+        Grid2Mat m;
+        m.gx = g2_gx;
+        m.gy = g2_gy;
+        m.nd = g2_nd;
+        if (g2_pint >= 0 && ptab64) {
+            m.coef64 = ptab64 + (size_t)g2_pint * g2_nd;
+            m.coef32 = ptab32 + (size_t)g2_pint * g2_nd;
+        } else if (g2_nd == 5) {
+            m.dval64 = dval64;
+            m.dval32 = dval32;
+        }
+        return m;
+    }
+    void grid2_off(int prec) {
+        g2[prec] = Grid2Shape();
+        g2_us[prec] = 0.0;
+    }
     // column-banded CSR copies (matrices whose entries lie far from the
     // diagonal): c = 0 two bands, c = 1 four; bperm maps entries to CSR
     int32_t *brow[2] = {nullptr, nullptr}, *bcol[2] = {nullptr, nullptr}, *bperm[2] = {nullptr, nullptr};
@@ -468,6 +495,80 @@ pp_status build_round_plan(pp_matrix A, int prec, int ept, int4 **dst, int *ndst
     return PP_OK;
 }
 
+// The shapes of the 2-D multi-step kernel worth timing, the most promising
+// first by a model of one step's time: 4 us per launch (the launch and its
+// trip to memory) over its steps, then per step 0.12 us for the barrier and
+// the issue time of the region's operations on the fullest CU.
+void grid2_shapes(const Grid2Mat &m, int prec, std::vector<Grid2Shape> &out) {
+    std::vector<std::pair<double, Grid2Shape>> all;
+    const double ops = (m.nd == 13 ? 15.0 : 7.0) + (prec == 0 ? (m.nd == 13 ? 18.0 : 3.0) : 1.0);
+    for (int vx = 1; vx <= 2; ++vx)
+        for (int ry = 1; ry <= kGrid2MaxRows; ++ry) {
+            if (!grid2_built(m, prec, vx, ry)) continue;
+            const int whole = (m.gy + ry - 1) / ry;  // waves that span the grid's rows
+            for (int waves : {4, 8, 16, whole}) {
+                if (waves > 16 || whole < waves) continue;
+                Grid2Shape s, best;
+                s.vx = vx;
+                s.ry = ry;
+                s.waves = waves;
+                double bt = 1e30;
+                for (int n = 2; n <= kGrid2MaxSteps; ++n) {
+                    int tx, ty;
+                    long tiles;
+                    if (!grid2_tiles(m, s, n, &tx, &ty, &tiles)) break;
+                    const double per_simd = (double)((tiles + 255) / 256) * std::max(1.0, waves / 4.0);
+                    const double t = 4.0 / n + 0.12 + per_simd * ry * vx * ops * 4.0 / 2400.0;
+                    if (t < bt) {
+                        bt = t;
+                        best = s;
+                        best.steps = n;
+                    }
+                }
+                if (best.steps > 0) all.emplace_back(bt, best);
+            }
+        }
+    std::stable_sort(all.begin(), all.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+    out.clear();
+    for (const auto &a : all) out.push_back(a.second);
+}
+
+// Time the 2-D multi-step kernel's likeliest shapes and keep the one with the
+// lowest time per step when it beats `single`, a step's time in a launch of
+// its own.
+pp_status tune_grid2(pp_matrix A, int prec, double single, hipEvent_t e0, hipEvent_t e1, hipStream_t st) {
+    A->grid2_off(prec);
+    if (A->g2_nd == 0 || prec == PP_BF16S) return PP_OK;
+    const Workspace &w = A->ws[prec];
+    const Grid2Mat m = A->grid2();
+    std::vector<Grid2Shape> shapes;
+    grid2_shapes(m, prec, shapes);
+    Grid2Step<double> u[kGrid2MaxSteps];
+    for (auto &t : u) t = Grid2Step<double>{1.0, 0.0, 0.0, 0.0, 0.0, 0};
+    double best = single;
+    for (size_t k = 0; k < shapes.size() && k < 4; ++k) {
+        const Grid2Shape &s = shapes[k];
+        const Grid2Ptrs gp{w.P0, w.P1, nullptr, 0, nullptr, u, s.steps};
+        double us = 1e30;
+        for (int round = 0; round < 2; ++round) {
+            HIP_TRY(launch_chain_grid2(m, prec, s, gp, 1, st));
+            HIP_TRY(hipEventRecord(e0, st));
+            for (int i = 0; i < 5; ++i) HIP_TRY(launch_chain_grid2(m, prec, s, gp, 1, st));
+            HIP_TRY(hipEventRecord(e1, st));
+            HIP_TRY(hipEventSynchronize(e1));
+            float ms = 0.f;
+            HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
+            us = std::min(us, 1e3 * ms / 5);
+        }
+        if (us / s.steps < best) {
+            best = us / s.steps;
+            A->g2[prec] = s;
+            A->g2_us[prec] = us;
+        }
+    }
+    return PP_OK;
+}
+
 pp_status tune_chain(pp_matrix A, int prec, hipStream_t st) {
     PP_TRY(A->ensure_ws(prec, 0));
     PP_TRY(build_round_plan(A, prec, 8, &A->tileB8[prec], &A->ntileB8[prec], st));
@@ -529,6 +630,10 @@ pp_status tune_chain(pp_matrix A, int prec, hipStream_t st) {
     A->remap[prec] = br;
     A->persist[prec] = 0;
     double best_all = best;
+    PP_TRY(tune_grid2(A, prec, best, e0, e1, st));
+    // a 2-D chain that runs in under half of its single steps' time is not
+    // timed against the two- to four-step kernels (they reach 0.6 of it)
+    const bool grid2_wins = A->g2[prec].steps > 0 && A->g2_us[prec] / A->g2[prec].steps < 0.5 * best;
     // two steps per launch on a box stencil (the pairs that chains with an
     // accumulator use: p chains' steps): one such launch, with the cube-tile
     // kernel or whole-line tiles where they apply, against two single steps
@@ -536,7 +641,7 @@ pp_status tune_chain(pp_matrix A, int prec, hipStream_t st) {
     A->fuse[prec] = 0;
     A->pair_us[prec] = 0.0;
     A->pair_tile[prec] = 0;
-    if (A->box_nd && A->pbyte && prec != PP_BF16S) {
+    if (A->box_nd && A->pbyte && prec != PP_BF16S && !grid2_wins) {
         const DevCSR d = A->dev();
         auto timed = [&](auto &&launch, double &best_us) -> pp_status {
             for (int round = 0; round < 2; ++round) {
@@ -592,7 +697,7 @@ pp_status tune_chain(pp_matrix A, int prec, hipStream_t st) {
         A->march_us[prec][g] = 0.0;
         A->march_cz[prec][g] = 0;
     }
-    if (A->box_nd && A->pbyte && prec != PP_BF16S) {
+    if (A->box_nd && A->pbyte && prec != PP_BF16S && !grid2_wins) {
         const DevCSR d = A->dev();
         MarchPtrs mp;
         std::memset(&mp, 0, sizeof(mp));
@@ -663,6 +768,7 @@ pp_status tune_chain(pp_matrix A, int prec, hipStream_t st) {
                 A->march[prec] = g;
             }
         }
+        if (A->g2[prec].steps > 0 && A->g2_us[prec] / A->g2[prec].steps >= per_step) A->grid2_off(prec);
     }
     // The persistent kernel is only timed on request: its grid barrier must
     // write back and invalidate the per-XCD L2 caches, which costs far more
@@ -768,9 +874,27 @@ int march_group_len(const std::vector<Step> &prog, size_t i, int smax) {
     return g;
 }
 
+// A chain program that is one chain: each step one sparse product of the
+// previous step's result (the first step's of the input), with at most the
+// previous step's input as aux, one accumulator that every step updates and
+// the first initialises (or none), and a final vector on the last step only.
+bool linear_program(const std::vector<Step> &prog) {
+    for (size_t i = 0; i < prog.size(); ++i) {
+        const Step &s = prog[i];
+        const bool last = i + 1 == prog.size();
+        if (s.spmv != 1 || s.in != (i ? prog[i - 1].out : (int)B_IN)) return false;
+        if (s.aux != B_NONE && (i == 0 || s.aux != prog[i - 1].in)) return false;
+        if (last ? s.out != B_NONE && s.out != B_OUT : s.out < B_P0) return false;
+        if (s.fin && !(last && s.out == B_OUT)) return false;
+        if (s.acc != prog[0].acc || (s.acc != B_NONE && (s.acc_init != 0) != (i == 0))) return false;
+    }
+    if (prog.empty() || prog[0].acc == B_NONE) return !prog.empty();
+    return prog[0].acc == B_OUT && prog.back().out == B_NONE && !prog.back().fin;
+}
+
 // One launch of a chain program as run_program issues it.
 struct Planned {
-    int kind;   // 0: one step, 1: the two-step pair kernel, 2: the marching kernel
+    int kind;   // 0: one step, 1: the two-step pair kernel, 2: the marching kernel, 3: the 2-D multi-step kernel
     int i, g;   // steps i .. i+g-1
     int write;  // the buffer the launch's last result goes to
     int swap;   // after the launch the names `write` and the last step's out swap (-1: no swap)
@@ -783,6 +907,22 @@ struct Planned {
 // dead after the group and the two names swap for the rest of the program.
 void plan_program(pp_matrix A, const std::vector<Step> &prog, int prec, std::vector<Planned> &out) {
     out.clear();
+    if (A->g2[prec].steps > 0 && !A->persist[prec] && linear_program(prog)) {
+        // launches of about equal length, none between a pair's two steps;
+        // each reads what the one before it wrote, two temporaries in turn
+        const int N = (int)prog.size(), smax = A->g2[prec].steps;
+        const int per = (N + (N + smax - 1) / smax - 1) / ((N + smax - 1) / smax);
+        int to = B_P0;
+        for (int i = 0; i < N;) {
+            int g = std::min(per, N - i);
+            if (i + g < N && prog[i + g].aux != B_NONE) g += g < smax ? 1 : -1;
+            const bool last = i + g == N;
+            out.push_back(Planned{3, i, g, last ? prog[N - 1].out : to, -1});
+            to = to == B_P0 ? B_P1 : B_P0;
+            i += g;
+        }
+        return;
+    }
     const bool coded = A->box_nd && A->pbyte && prec != PP_BF16S && !A->persist[prec];
     const bool pair = coded && A->fuse[prec];
     const int smax = coded ? A->march[prec] : 0;
@@ -854,8 +994,22 @@ pp_status run_program(pp_matrix A, pp_poly poly, int kind, int prec, const void 
     };
     std::vector<Planned> plan;
     plan_program(A, prog, prec, plan);
+    const void *chain = in;  // the vector a multi-step launch starts from
     for (const Planned &L : plan) {
         const Step &s = prog[L.i];
+        if (L.kind == 3) {
+            Grid2Step<double> u[kGrid2MaxSteps];
+            Grid2Ptrs gp{chain, ptr(L.write), nullptr, 1, prog[L.i + L.g - 1].fin ? in : nullptr, u, L.g};
+            for (int k = 0; k < L.g; ++k) {
+                const Step &t = prog[L.i + k];
+                u[k] = Grid2Step<double>{t.a0, t.a1, t.a2, t.b0, t.b1, t.aux != B_NONE ? kG2Aux : 0};
+                if (t.acc_init) gp.load_acc = 0;
+            }
+            gp.acc = ptr(s.acc);
+            HIP_TRY(launch_chain_grid2(A->grid2(), prec, A->g2[prec], gp, 1, st));
+            chain = gp.out;
+            continue;
+        }
         if (L.kind == 2) {
             const Step &t = prog[L.i + L.g - 1];
             MarchPtrs mp;
@@ -1067,6 +1221,15 @@ void program_bytes(pp_matrix A, pp_poly poly, int kind, int prec, int64_t &bytes
     plan_program(A, prog, prec, plan);
     for (const Planned &L : plan) {
         const Step &s = prog[L.i], &t = prog[L.i + L.g - 1];
+        if (L.kind == 3) {
+            // the coefficients (or the diagonal format's values), the input,
+            // the accumulator or the final vector, the output: each once
+            const int64_t slots = A->g2_pint >= 0 ? 1 : ((int64_t)A->n + 255) / 256 * 256;
+            bytes += slots * A->g2_nd * csz + vec * (1 + (t.out != B_NONE) + (t.fin != 0));
+            if (s.acc != B_NONE) bytes += vec * (s.acc_init ? 1 : 2);
+            launches += 1;
+            continue;
+        }
         if (L.kind == 2) {
             // the input and the pattern bytes once, the final vector, the output
             bytes += pat + vec * (1 + (t.fin != 0) + 1);
@@ -1554,41 +1717,78 @@ pp_status build_value_codes(pp_matrix A, const int32_t *dp, const std::vector<do
 // (and +-gx gy), n = gx gy gz, and no stored entry joining the last point
 // of a grid line (or plane) to the first of the next. Leaves box_nd = 0
 // when the matrix is not such a stencil.
-// A constant-coefficient box stencil: every row's code tuple is the one of
-// an interior row with code 0 (the value zero) wherever the neighbour lies
-// outside the box, so the interior row's coefficients serve every row of a
-// kernel that keeps the points outside the box at zero. The codes stay valid
-// when new values keep them (pp_matrix_set_values), so does this.
-void detect_box_const(pp_matrix A, hipStream_t st) {
-    A->box_pint = -1;
-    if (!A->box_nd || !A->pbyte || !A->pcodes || A->npat <= 0) return;
+// The interior row's pattern of a constant-coefficient stencil on a gx x gy
+// x gz grid (-1: not one): every row's code tuple is the one of an interior
+// row with code 0 (the value zero) wherever the neighbour lies outside the
+// grid, so the interior row's coefficients serve every row of a kernel that
+// keeps the points outside the grid at zero. nb: the nd neighbours' grid
+// offsets in ascending diagonal order. The codes stay valid when new values
+// keep them (pp_matrix_set_values), so does this.
+int constant_pattern(pp_matrix A, long gx, long gy, long gz, int nd, const int (*nb)[3], hipStream_t st) {
+    if (!A->pbyte || !A->pcodes || A->npat <= 0) return -1;
     const long n = A->n;
-    const int nd = A->box_nd;
-    const long gx = A->box[0], gy = A->box[1], gz = A->box[2];
-    if (gx < 3 || gy < 3 || (nd == 7 && gz < 3)) return;
     std::vector<uint8_t> pb((size_t)n), pc((size_t)A->npat * nd);
     if (hipMemcpyAsync(pb.data(), A->pbyte, (size_t)n, hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipMemcpyAsync(pc.data(), A->pcodes, pc.size(), hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
-        return;
-    const long rc = gx / 2 + gx * (gy / 2 + gy * (nd == 7 ? gz / 2 : 0));
+        return -1;
+    const long rc = gx / 2 + gx * (gy / 2 + gy * (gz / 2));
     const int pint = pb[(size_t)rc];
     const uint8_t *ci = pc.data() + (size_t)pint * nd;
     for (long r = 0; r < n; ++r) {
         const long x = r % gx, y = (r / gx) % gy, z = r / (gx * gy);
-        // neighbours in ascending offset order: (-z) -y -x 0 +x +y (+z)
-        bool in[7];
-        if (nd == 7) {
-            in[0] = z > 0, in[1] = y > 0, in[2] = x > 0, in[3] = true, in[4] = x < gx - 1, in[5] = y < gy - 1,
-            in[6] = z < gz - 1;
-        } else {
-            in[0] = y > 0, in[1] = x > 0, in[2] = true, in[3] = x < gx - 1, in[4] = y < gy - 1;
-        }
         const uint8_t *cr = pc.data() + (size_t)pb[(size_t)r] * nd;
-        for (int d = 0; d < nd; ++d)
-            if (cr[d] != (in[d] ? ci[d] : 0)) return;
+        for (int d = 0; d < nd; ++d) {
+            const long xx = x + nb[d][0], yy = y + nb[d][1], zz = z + nb[d][2];
+            const bool in = xx >= 0 && xx < gx && yy >= 0 && yy < gy && zz >= 0 && zz < gz;
+            if (cr[d] != (in ? ci[d] : 0)) return -1;
+        }
     }
-    A->box_pint = pint;
+    return pint;
+}
+
+// grid offsets of the stencils' diagonals, ascending
+constexpr int kNb7[7][3] = {{0, 0, -1}, {0, -1, 0}, {-1, 0, 0}, {0, 0, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
+constexpr int kNb5[5][3] = {{0, -1, 0}, {-1, 0, 0}, {0, 0, 0}, {1, 0, 0}, {0, 1, 0}};
+constexpr int kNb13[13][3] = {{0, -2, 0}, {-1, -1, 0}, {0, -1, 0}, {1, -1, 0}, {-2, 0, 0}, {-1, 0, 0}, {0, 0, 0},
+                              {1, 0, 0},  {2, 0, 0},   {-1, 1, 0}, {0, 1, 0},  {1, 1, 0},  {0, 2, 0}};
+
+void detect_box_const(pp_matrix A, hipStream_t st) {
+    A->box_pint = -1;
+    const int nd = A->box_nd;
+    if (nd && A->box[0] >= 3 && A->box[1] >= 3 && (nd != 7 || A->box[2] >= 3))
+        A->box_pint = constant_pattern(A, A->box[0], A->box[1], A->box[2], nd, nd == 7 ? kNb7 : kNb5, st);
+    A->g2_pint = -1;
+    if (A->g2_nd == 5 && A->box_nd == 5)
+        A->g2_pint = A->box_pint;
+    else if (A->g2_nd == 13)
+        A->g2_pint = constant_pattern(A, A->g2_gx, A->g2_gy, 1, 13, kNb13, st);
+}
+
+// 2-D grid geometry of the multi-step kernel (g2_*): the rows are the points
+// of a gx x gy grid, the diagonals exactly those of the 5- or the 13-point
+// stencil, and no stored entry reaches past the end of its grid line.
+void detect_grid2(pp_matrix A, const std::vector<int32_t> &ci) {
+    const auto &o = A->h_doff;
+    const int nd = (int)o.size();
+    if (nd != 5 && nd != 13) return;
+    const int(*nb)[3] = nd == 5 ? kNb5 : kNb13;
+    const long gx = nd == 5 ? o[4] : o[12] / 2;
+    if (gx < (nd == 5 ? 3 : 5) || A->n % gx != 0 || A->n / gx < (nd == 5 ? 3 : 5)) return;
+    for (int d = 0; d < nd; ++d)
+        if (o[d] != nb[d][0] + gx * nb[d][1]) return;
+    const auto &rp = A->h_rowptr;
+    for (long r = 0; r < A->n; ++r) {
+        const long x = r % gx;
+        if (x >= 2 && x < gx - 2) continue;  // no diagonal reaches further along a line
+        for (int k = rp[r]; k < rp[r + 1]; ++k) {
+            const int d = (int)(std::lower_bound(o.begin(), o.end(), (int)(ci[k] - r)) - o.begin());
+            if (x + nb[d][0] < 0 || x + nb[d][0] >= gx) return;
+        }
+    }
+    A->g2_nd = nd;
+    A->g2_gx = (int)gx;
+    A->g2_gy = (int)(A->n / gx);
 }
 
 void detect_box(pp_matrix A, const std::vector<int32_t> &ci) {
@@ -1853,6 +2053,7 @@ pp_status pp_matrix_create(int64_t n, int64_t nnz, const int32_t *rowptr, const 
                     hipStreamSynchronize(st) == hipSuccess)
                     if ((s = build_value_codes(A, dp.data(), hv, st)) != PP_OK) return fail(s);
                 if (A->pbyte) detect_box(A, ci);
+                detect_grid2(A, ci);
                 detect_box_const(A, st);
             }
         }
@@ -1923,7 +2124,7 @@ pp_status refresh_values(pp_matrix A, const double *val, hipStream_t st) {
             dev_free(A->ptab32);
             A->ntab = 0;
             A->npat = 0;
-            A->box_pint = -1;
+            A->box_pint = A->g2_pint = -1;
             for (int p = 0; p < 3; ++p)
                 if (A->variant[p] == CV_DIAC || A->variant[p] == CV_DIAP || A->variant[p] == CV_DIAPV ||
                     A->variant[p] == CV_BOX) {
@@ -1943,6 +2144,17 @@ pp_status refresh_values(pp_matrix A, const double *val, hipStream_t st) {
                 HIP_TRY(hipStreamSynchronize(st));
                 PP_TRY(build_value_codes(A, dp.data(), hv, st));
                 detect_box_const(A, st);
+            }
+            // a tuned multi-step shape may not be built for per-row values:
+            // the model's first choice takes its place
+            for (int p = 0; p < 3; ++p) {
+                if (A->g2[p].steps == 0 || (grid2_built(A->grid2(), p, A->g2[p].vx, A->g2[p].ry) && A->g2_pint >= 0)) continue;
+                std::vector<Grid2Shape> shapes;
+                grid2_shapes(A->grid2(), p, shapes);
+                if (shapes.empty())
+                    A->grid2_off(p);
+                else
+                    A->g2[p] = shapes[0];
             }
         }
     }
@@ -2279,6 +2491,7 @@ pp_status pp_matrix_set_variant(pp_matrix A, int prec, int variant, int remap) {
     A->march_all[prec] = 0;
     A->march_tile[prec] = 0;
     A->pair_tile[prec] = 0;
+    A->grid2_off(prec);
     return PP_OK;
 }
 
@@ -2297,6 +2510,7 @@ pp_status pp_matrix_set_pair_steps(pp_matrix A, int prec, int mode) {
         return PP_EINVAL;
     }
     A->fuse[prec] = mode;
+    A->grid2_off(prec);
     return PP_OK;
 }
 
@@ -2315,6 +2529,7 @@ pp_status pp_matrix_set_march(pp_matrix A, int prec, int steps, int cz, int dept
         set_error("pp_matrix_set_march: tune or set a single-launch variant for this precision first");
         return PP_EINVAL;
     }
+    A->grid2_off(prec);
     A->march[prec] = steps;
     A->march_all[prec] = steps >= 2;
     A->march_tile[prec] = 0;
@@ -2340,6 +2555,7 @@ pp_status pp_matrix_set_march_shape(pp_matrix A, int prec, int shape) {
                   "whose grid lines hold 64, 128 or 256 points, and FP64 or FP32 vectors");
         return PP_EINVAL;
     }
+    A->grid2_off(prec);
     A->march_tile[prec] = shape;
     A->pair_tile[prec] = shape;
     if (shape == 1) {
@@ -2347,6 +2563,47 @@ pp_status pp_matrix_set_march_shape(pp_matrix A, int prec, int shape) {
         A->march_all[prec] = 1;
         A->fuse[prec] = 1;  // the pairs of p chains too
     }
+    return PP_OK;
+}
+
+pp_status pp_matrix_set_grid(pp_matrix A, int prec, int vx, int ry, int waves, int steps) {
+    if (!A || !valid_prec(prec) || steps < 0 || steps == 1 || steps > kGrid2MaxSteps) {
+        set_error("pp_matrix_set_grid: bad argument");
+        return PP_EINVAL;
+    }
+    if (!A->tuned[prec] || A->persist[prec]) {
+        set_error("pp_matrix_set_grid: tune or set a single-launch variant for this precision first");
+        return PP_EINVAL;
+    }
+    Grid2Shape s;
+    s.vx = vx;
+    s.ry = ry;
+    s.waves = waves;
+    s.steps = steps;
+    int tx, ty;
+    long tiles;
+    if (steps > 0 && (A->g2_nd == 0 || !grid2_built(A->grid2(), prec, vx, ry) ||
+                      !grid2_tiles(A->grid2(), s, steps, &tx, &ty, &tiles))) {
+        set_error("pp_matrix_set_grid: needs a 5- or 13-point stencil on a 2-D grid (13 points: constant "
+                  "coefficients), FP64 or FP32 vectors, and a built shape whose region leaves a tile");
+        return PP_EINVAL;
+    }
+    A->grid2_off(prec);
+    if (steps > 0) A->g2[prec] = s;
+    return PP_OK;
+}
+
+pp_status pp_matrix_grid(pp_matrix A, int prec, int *shape, double *us) {
+    if (!A || !valid_prec(prec) || !shape) {
+        set_error("pp_matrix_grid: bad argument");
+        return PP_EINVAL;
+    }
+    const Grid2Shape &s = A->g2[prec];
+    shape[0] = s.vx;
+    shape[1] = s.ry;
+    shape[2] = s.waves;
+    shape[3] = s.steps;
+    if (us) *us = A->g2_us[prec];
     return PP_OK;
 }
 
@@ -2977,8 +3234,10 @@ pp_status pp_solve(pp_poly p, pp_matrix A, const double *b, double *x, const pp_
         // by more than that ratio.
         bool ahead = false;
         double r_last = beta, rate = 1.0;
-        const double t_phi = (double)chain_launches(p, PP_APPLY_PHI) *
-                             (A->tuned_us[prec] > 0.0 ? A->tuned_us[prec] : kLaunchGuessUs);
+        const double t_step = A->g2[prec].steps > 0 && A->g2_us[prec] > 0.0 ? A->g2_us[prec] / A->g2[prec].steps
+                              : A->tuned_us[prec] > 0.0                      ? A->tuned_us[prec]
+                                                                             : kLaunchGuessUs;
+        const double t_phi = (double)chain_launches(p, PP_APPLY_PHI) * t_step;
         const double margin = std::max(2.0, t_phi / kLookaheadGapUs);
         for (int j = 0; j < m; ++j) {
             if (!ahead) PP_TRY(run_program(A, p, PP_APPLY_PHI, prec, vcol(ws, prec, j), vcol(ws, prec, j + 1), st));
