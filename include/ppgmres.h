@@ -582,6 +582,21 @@ pp_status pp_batch_orth(pp_batch B, int *delayed);
 pp_status pp_batch_set_chain_config(pp_batch B, int prec, int nrhs, int format, int spw, int remap);
 pp_status pp_batch_chain_config(pp_batch B, int prec, int nrhs, int *format, int *spw, int *remap, double *us);
 
+/* Many chain steps per launch of a batch with a box copy (regions of 64 x
+ * waves ry points in registers, as pp_matrix_set_grid with one column a
+ * lane), whatever format its single steps read. pp_batch_tune times the
+ * likeliest shapes and keeps the fastest when it beats one step per launch.
+ *   pp_batch_set_grid: forces a shape for (prec, nrhs) (ry 2, 3, 4 or 6, steps
+ *     2..31; steps 0 turns it off); PP_EINVAL without a box copy, with a
+ *     format forced by pp_batch_set_format, before (prec, nrhs) is tuned or
+ *     set, for a shape that is not built or leaves no tile, and for bfloat16
+ *     vectors. New values, pp_batch_set_format and pp_batch_set_chain_config
+ *     turn it off.
+ *   pp_batch_grid: shape (host int[3]) = {ry, waves, steps} in use (steps 0:
+ *     off), us the tuned time of one launch over the batch (0: forced). */
+pp_status pp_batch_set_grid(pp_batch B, int prec, int nrhs, int ry, int waves, int steps);
+pp_status pp_batch_grid(pp_batch B, int prec, int nrhs, int *shape, double *us);
+
 void pp_batch_destroy(pp_batch B);
 
 /* One polynomial per system (Algorithm 4 step 1 for every system at once):

@@ -99,6 +99,8 @@ SIGNATURES = {
     "pp_batch_tune": (c_int, [c_void_p, c_int, c_int, c_void_p]),
     "pp_batch_set_chain_config": (c_int, [c_void_p, c_int, c_int, c_int, c_int, c_int]),
     "pp_batch_chain_config": (c_int, [c_void_p, c_int, c_int, P_int, P_int, P_int, P_double]),
+    "pp_batch_set_grid": (c_int, [c_void_p, c_int, c_int, c_int, c_int, c_int]),
+    "pp_batch_grid": (c_int, [c_void_p, c_int, c_int, P_int, P_double]),
     "pp_batch_destroy": (None, [c_void_p]),
     "pp_batch_setup": (c_int, [c_void_p, c_void_p, c_int, c_int, c_void_p, ctypes.POINTER(c_void_p),
                                ctypes.POINTER(SetupInfo)]),

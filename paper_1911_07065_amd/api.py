@@ -707,6 +707,16 @@ class Batch:
                                         ctypes.byref(rm), ctypes.byref(us)), "pp_batch_chain_config")
         return self.BATCH_FORMATS[f.value], spw.value, rm.value, us.value
 
+    def set_grid(self, R: int, prec: str, ry: int, waves: int, steps: int):
+        """Up to `steps` chain steps per launch for (prec, R) of a batch with a box copy (steps 0: off)."""
+        check(lib.pp_batch_set_grid(self.handle, PREC[prec], int(R), int(ry), int(waves), int(steps)), "pp_batch_set_grid")
+
+    def grid(self, R: int, prec: str = "fp32"):
+        """((rows per wave, waves, steps), tuned us per launch) of the batched multi-step kernel (steps 0: off)."""
+        sh, us = (ctypes.c_int * 3)(), ctypes.c_double()
+        check(lib.pp_batch_grid(self.handle, PREC[prec], int(R), sh, ctypes.byref(us)), "pp_batch_grid")
+        return tuple(sh), us.value
+
     def set_values(self, val):
         """New values (device or host float64[nnz], the concatenated systems'
         entries in CSR order); drops the pattern-coded copy."""

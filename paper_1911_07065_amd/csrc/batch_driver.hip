@@ -189,11 +189,58 @@ struct pp_batch_s {
         double us = 0.0;
     };
     ChainCfg cfg[3][5];
+    // many steps per launch (box copy) per precision and right-hand-side
+    // count: the tiles (grid_tiles, owned) and shape, steps 0: off
+    BatchGrid grid[3][5];
+    int4 *grid_tiles[3][5] = {};
+    double grid_us[3][5] = {};
+    void grid_off(int prec, int R) {
+        dev_free(grid_tiles[prec][R]);
+        grid[prec][R] = BatchGrid();
+        grid_us[prec][R] = 0.0;
+    }
+    void grids_off() {
+        for (int p = 0; p < 3; ++p)
+            for (int r = 0; r < 5; ++r) grid_off(p, r);
+    }
+    std::vector<int32_t> h_bgx;  // line length of every system's grid (box copy)
+    // The shape's tiles over every system, uploaded (both tile lists in one
+    // allocation); off when a region leaves no tile.
+    pp_status grid_on(int prec, int R, int ry, int waves, int steps, hipStream_t st) {
+        grid_off(prec, R);
+        const int aw = std::min(waves, batch_grid_max_waves(prec == 0 ? 8 : 4, R, ry, true));
+        std::vector<int4> t;
+        size_t first = 0;
+        for (int h : {ry * waves, ry * aw}) {
+            first = t.size();
+            for (int s = 0; s < nsys; ++s) {
+                const int gx = h_bgx[s], gy = (int)((row_off[s + 1] - row_off[s]) / gx);
+                const int tx = gx <= 64 ? gx : 64 - 2 * steps, ty = gy <= h ? gy : h - 2 * steps;
+                if (tx < 1 || ty < 1) return PP_OK;
+                for (int y = 0; y < gy; y += ty)
+                    for (int x = 0; x < gx; x += tx) t.push_back(int4{s, x, y, 0});
+            }
+        }
+        PP_TRY(dev_alloc(&grid_tiles[prec][R], t.size()));
+        HIP_TRY(hipMemcpyAsync(grid_tiles[prec][R], t.data(), sizeof(int4) * t.size(), hipMemcpyHostToDevice, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        BatchGrid &g = grid[prec][R];
+        g.tile = grid_tiles[prec][R];
+        g.ntiles = (int)first;
+        g.acc_tile = g.tile + first;
+        g.acc_ntiles = (int)(t.size() - first);
+        g.ry = ry;
+        g.waves = waves;
+        g.acc_waves = aw;
+        g.steps = steps;
+        return PP_OK;
+    }
     bool format_forced = false;  // pp_batch_set_format: the tuner keeps the format
     bool format_ok(int f) const { return f == 0 || (f == 1 && pnd > 0) || (f == 2 && has_box && pnd > 0); }
-    BatchSell sell(int prec, bool masked = false, int R = 1) const {
+    // use_box: the box copy whatever the format (the multi-step kernel's)
+    BatchSell sell(int prec, bool masked = false, int R = 1, bool use_box = false) const {
         const ChainCfg &c = cfg[prec][R];
-        const int fmt = (c.tuned && !format_forced && format_ok(c.format)) ? c.format : format;
+        const int fmt = use_box ? 2 : (c.tuned && !format_forced && format_ok(c.format)) ? c.format : format;
         BatchSell s;
         s.spw = c.tuned ? c.spw : 1;
         s.remap = c.tuned ? c.remap : 1;
@@ -229,6 +276,7 @@ struct pp_batch_s {
         dev_free(ptab32);
         pnd = 0;
         format = 0;
+        grids_off();
     }
     BatchBlocks blocks(bool masked = false) const {
         BatchBlocks b;
@@ -331,6 +379,7 @@ struct pp_batch_s {
         dev_free(desc_res);
         dev_free(act);
         dev_free(ones);
+        grids_off();
         dev_free(kdev);
         if (actpin) (void)hipHostFree(actpin);
         if (kpin) (void)hipHostFree(kpin);
@@ -375,26 +424,88 @@ pp_status upload(const std::vector<PStep> &h, PStep **dst, hipStream_t st) {
     return PP_OK;
 }
 
-// Per-system programs padded to a common length with skipped steps.
-pp_status upload_programs(pp_batch B, const pp_poly *polys, int kind, PStep **dst, int *K, hipStream_t st) {
-    int kmax = 0;
-    for (int s = 0; s < B->nsys; ++s) {
-        const auto &prog = kind == PP_APPLY_P ? polys[s]->prog_p : polys[s]->prog_phi;
-        kmax = std::max(kmax, (int)prog.size());
+// Per-system programs of one kind, padded to a common length K with skipped
+// steps, and per precision their segments for the multi-step kernel (L
+// launches; null: one launch per step).
+struct BatchProg {
+    PStep *steps = nullptr;
+    int K = 0;
+    BatchSeg *segs[3] = {nullptr, nullptr, nullptr};
+    int L[3] = {0, 0, 0};
+    bool acc = false;  // the programs have an accumulator
+    ~BatchProg() {
+        dev_free(steps);
+        for (auto &p : segs) dev_free(p);
     }
+};
+
+const std::vector<Step> &prog_of(const pp_poly p, int kind) { return kind == PP_APPLY_P ? p->prog_p : p->prog_phi; }
+
+pp_status upload_programs(pp_batch B, const pp_poly *polys, int kind, BatchProg &P, hipStream_t st) {
+    int kmax = 0;
+    for (int s = 0; s < B->nsys; ++s) kmax = std::max(kmax, (int)prog_of(polys[s], kind).size());
     std::vector<PStep> h((size_t)B->nsys * kmax, skip_step());
     for (int s = 0; s < B->nsys; ++s) {
-        const auto &prog = kind == PP_APPLY_P ? polys[s]->prog_p : polys[s]->prog_phi;
+        const auto &prog = prog_of(polys[s], kind);
         for (size_t k = 0; k < prog.size(); ++k) h[(size_t)s * kmax + k] = pstep_of(prog[k]);
     }
-    *K = kmax;
-    return upload(h, dst, st);
+    P.K = kmax;
+    P.acc = kind == PP_APPLY_P;
+    return upload(h, &P.steps, st);
 }
 
-pp_status run_bprog(pp_batch B, int prec, int R, const PStep *desc, int K, const void *in, void *out,
-                    const BWork &w, hipStream_t st, bool masked = false) {
+// The programs' segments for precision prec's multi-step launches, if it has
+// them and every program is one chain. Each system cuts its own program; one
+// with fewer segments than the longest sits out the last launches.
+pp_status upload_segments(pp_batch B, const pp_poly *polys, int kind, int prec, int R, BatchProg &P, hipStream_t st) {
+    const int smax = B->grid[prec][R].steps;
+    if (smax == 0 || P.segs[prec]) return PP_OK;
+    std::vector<std::vector<int>> lens(B->nsys);
+    int L = 0;
+    for (int s = 0; s < B->nsys; ++s) {
+        const auto &prog = prog_of(polys[s], kind);
+        if (!linear_program(prog) || (prog[0].acc != B_NONE) != P.acc) return PP_OK;
+        lens[s] = split_program(prog, smax);
+        L = std::max(L, (int)lens[s].size());
+    }
+    std::vector<BatchSeg> h((size_t)B->nsys * L);
+    std::memset(h.data(), 0, sizeof(BatchSeg) * h.size());
+    for (int s = 0; s < B->nsys; ++s) {
+        const auto &prog = prog_of(polys[s], kind);
+        int i = 0, from = B_IN, to = B_P0;
+        for (size_t l = 0; l < lens[s].size(); ++l) {
+            const bool last = l + 1 == lens[s].size();
+            BatchSeg &g = h[(size_t)s * L + l];
+            g.first = i;
+            g.count = lens[s][l];
+            g.in = from;
+            g.out = last ? prog.back().out : to;
+            g.fin = last ? prog.back().fin : 0;
+            g.acc = prog[i].acc;
+            g.acc_init = prog[i].acc_init;
+            from = to;
+            to = to == B_P0 ? B_P1 : B_P0;
+            i += g.count;
+        }
+    }
+    PP_TRY(dev_alloc(&P.segs[prec], h.size()));
+    HIP_TRY(hipMemcpyAsync(P.segs[prec], h.data(), sizeof(BatchSeg) * h.size(), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    P.L[prec] = L;
+    return PP_OK;
+}
+
+pp_status run_bprog(pp_batch B, int prec, int R, const BatchProg &P, const void *in, void *out, const BWork &w,
+                    hipStream_t st, bool masked = false) {
     void *bufs[5] = {(void *)in, out, w.P(0), w.P(1), w.P(2)};
-    for (int k = 0; k < K; ++k) HIP_TRY(launch_bchain(B->sell(prec, masked, R), prec, R, desc, K, k, bufs, st));
+    if (P.segs[prec]) {
+        const BatchSell X = B->sell(prec, masked, R, true);
+        for (int l = 0; l < P.L[prec]; ++l)
+            HIP_TRY(launch_bgrid(X, B->grid[prec][R], P.acc, prec, R, P.steps, P.K, P.segs[prec], P.L[prec], l, bufs, st));
+        return PP_OK;
+    }
+    const BatchSell S = B->sell(prec, masked, R);
+    for (int k = 0; k < P.K; ++k) HIP_TRY(launch_bchain(S, prec, R, P.steps, P.K, k, bufs, st));
     return PP_OK;
 }
 
@@ -403,6 +514,8 @@ pp_status run_bprog(pp_batch B, int prec, int R, const PStep *desc, int K, const
 // caller fixed it), slices per wave (1 or 2, pattern-coded format) and
 // workgroup order (XCD-aware or not), on the batch's own matrix, precision
 // and right-hand-side count; the fastest is kept for (prec, R).
+pp_status tune_bgrid(pp_batch B, int prec, int R, double single, hipEvent_t e0, hipEvent_t e1, hipStream_t st);
+
 pp_status tune_bchain(pp_batch B, int prec, int R, hipStream_t st) {
     PP_TRY(B->ensure(prec, std::max(B->ws[prec].m, 1), R));
     const BWork &w = B->ws[prec];
@@ -451,6 +564,80 @@ pp_status tune_bchain(pp_batch B, int prec, int R, hipStream_t st) {
     }
     c = best;
     c.tuned = 1;
+    return tune_bgrid(B, prec, R, best.us, e0, e1, st);
+}
+
+// Times the multi-step kernel's shapes over the whole batch (when it has the
+// box copy and the caller forced no format) and turns on the one with the
+// lowest time per step if that beats `single`, the best single-step launch. The shapes
+// timed are the four best by a model of one step: the launch's memory traffic
+// (the regions read, the tiles written, at a copy's 4.5 TB/s) and 4 us over
+// its steps, then the issue of the regions' operations.
+pp_status tune_bgrid(pp_batch B, int prec, int R, double single, hipEvent_t e0, hipEvent_t e1, hipStream_t st) {
+    B->grid_off(prec, R);
+    if (B->format_forced || !B->format_ok(2)) return PP_OK;
+    struct Cand {
+        double t;
+        int ry, waves, steps;
+    };
+    std::vector<Cand> all;
+    const double vb = prec == 0 ? 8.0 : 4.0, ops = prec == 0 ? 12.0 : 8.0;
+    for (int ry : {2, 3, 4, 6})
+        for (int waves : {4, 8, 16}) {
+            Cand best{1e30, ry, waves, 0};
+            for (int n = 2; batch_grid_ok(prec, R, ry, waves, n); ++n) {
+                double tiles = 0, pts = 0;
+                bool ok = true;
+                for (int s = 0; s < B->nsys && ok; ++s) {
+                    const int gx = B->h_bgx[s], gy = (int)((B->row_off[s + 1] - B->row_off[s]) / gx), h = ry * waves;
+                    const int tx = gx <= 64 ? gx : 64 - 2 * n, ty = gy <= h ? gy : h - 2 * n;
+                    ok = tx >= 1 && ty >= 1;
+                    if (ok) tiles += (double)((gx + tx - 1) / tx) * ((gy + ty - 1) / ty);
+                    pts += (double)gx * gy;
+                }
+                if (!ok) break;
+                const double region = 64.0 * ry * waves * R;
+                const double mem = (tiles * region + pts * R) * vb / 4.5e6;
+                const double issue = std::max(tiles / 256.0, 1.0) * (region / 64.0) * ops * 4.0 / 4.0 / 2400.0;
+                const double t = (4.0 + mem) / n + 0.12 + issue;
+                if (t < best.t) best = Cand{t, ry, waves, n};
+            }
+            if (best.steps > 0) all.push_back(best);
+        }
+    std::stable_sort(all.begin(), all.end(), [](const Cand &a, const Cand &b) { return a.t < b.t; });
+    const BWork &w = B->ws[prec];
+    // a program of the most steps: real roots, no accumulator
+    BatchProg P;
+    std::vector<PStep> h((size_t)B->nsys * kGrid2MaxSteps, pstep_of(Step{1, B_P0, B_NONE, B_P1, B_NONE, 0, 0, 1.0, 0.0, 0.0, 0.0, 0.0}));
+    PP_TRY(upload(h, &P.steps, st));
+    PP_TRY(dev_alloc(&P.segs[prec], B->nsys));
+    void *bufs[5] = {w.P(0), w.P(1), w.P(2), w.P(3), w.P(4)};
+    Cand best{single, 0, 0, 0};
+    for (size_t k = 0; k < all.size() && k < 4; ++k) {
+        const Cand &c = all[k];
+        PP_TRY(B->grid_on(prec, R, c.ry, c.waves, c.steps, st));
+        std::vector<BatchSeg> sg(B->nsys, BatchSeg{0, c.steps, B_IN, B_OUT, 0, -1, 0, 0});
+        HIP_TRY(hipMemcpyAsync(P.segs[prec], sg.data(), sizeof(BatchSeg) * sg.size(), hipMemcpyHostToDevice, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        const BatchSell S = B->sell(prec, false, R, true);
+        double us = 1e30;
+        for (int round = 0; round < 2; ++round) {
+            HIP_TRY(launch_bgrid(S, B->grid[prec][R], false, prec, R, P.steps, kGrid2MaxSteps, P.segs[prec], 1, 0, bufs, st));
+            HIP_TRY(hipEventRecord(e0, st));
+            for (int i = 0; i < 3; ++i)
+                HIP_TRY(launch_bgrid(S, B->grid[prec][R], false, prec, R, P.steps, kGrid2MaxSteps, P.segs[prec], 1, 0, bufs, st));
+            HIP_TRY(hipEventRecord(e1, st));
+            HIP_TRY(hipEventSynchronize(e1));
+            float ms = 0.f;
+            HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
+            us = std::min(us, 1e3 * ms / 3);
+        }
+        if (us / c.steps < best.t) best = Cand{us / c.steps, c.ry, c.waves, c.steps};
+    }
+    B->grid_off(prec, R);
+    if (best.steps == 0) return PP_OK;
+    PP_TRY(B->grid_on(prec, R, best.ry, best.waves, best.steps, st));
+    B->grid_us[prec][R] = best.t * best.steps;
     return PP_OK;
 }
 
@@ -655,6 +842,7 @@ pp_status build_batch_patterns(pp_batch B, const std::vector<int32_t> &rp, const
             return PP_EDEVICE;
         }
         B->has_box = 1;
+        B->h_bgx = bg;
     }
     return PP_OK;
 }
@@ -849,6 +1037,7 @@ pp_status pp_batch_set_format(pp_batch B, int format) {
     }
     B->format = format;
     B->format_forced = true;
+    B->grids_off();
     for (auto &row : B->cfg)
         for (auto &c : row) c.tuned = 0;
     return PP_OK;
@@ -902,6 +1091,43 @@ pp_status pp_batch_set_chain_config(pp_batch B, int prec, int nrhs, int format, 
     c.remap = remap;
     c.us = 0.0;
     B->format_forced = false;
+    B->grid_off(prec, nrhs);
+    return PP_OK;
+}
+
+pp_status pp_batch_set_grid(pp_batch B, int prec, int nrhs, int ry, int waves, int steps) {
+    if (!B || prec < 0 || prec > 2 || !(nrhs == 1 || nrhs == 2 || nrhs == 4) || steps < 0) {
+        set_error("pp_batch_set_grid: bad argument");
+        return PP_EINVAL;
+    }
+    if (steps == 0) {
+        B->grid_off(prec, nrhs);
+        return PP_OK;
+    }
+    if (!B->format_ok(2) || B->format_forced || !B->cfg[prec][nrhs].tuned ||
+        !batch_grid_ok(prec, nrhs, ry, waves, steps)) {
+        set_error("pp_batch_set_grid: needs a box copy, no forced format, a tuned or set chain configuration and a "
+                  "built shape, FP64 or FP32 vectors");
+        return PP_EINVAL;
+    }
+    PP_TRY(B->grid_on(prec, nrhs, ry, waves, steps, 0));
+    if (B->grid[prec][nrhs].steps == 0) {
+        set_error("pp_batch_set_grid: the region leaves no tile");
+        return PP_EINVAL;
+    }
+    return PP_OK;
+}
+
+pp_status pp_batch_grid(pp_batch B, int prec, int nrhs, int *shape, double *us) {
+    if (!B || prec < 0 || prec > 2 || !(nrhs == 1 || nrhs == 2 || nrhs == 4) || !shape) {
+        set_error("pp_batch_grid: bad argument");
+        return PP_EINVAL;
+    }
+    const BatchGrid &g = B->grid[prec][nrhs];
+    shape[0] = g.ry;
+    shape[1] = g.waves;
+    shape[2] = g.steps;
+    if (us) *us = B->grid_us[prec][nrhs];
     return PP_OK;
 }
 
@@ -1069,18 +1295,9 @@ pp_status pp_batch_solve(pp_batch B, const pp_poly *polys, int nrhs, const doubl
     PP_TRY(B->ensure(opts->inner, m, R));
     if (!B->cfg[opts->inner][R].tuned) PP_TRY(tune_bchain(B, opts->inner, R, st));
     const BatchBlocks bl = B->blocks();
-    PStep *dphi = nullptr, *dp = nullptr;
-    int Kphi = 0, Kp = 0;
-    PP_TRY(upload_programs(B, polys, PP_APPLY_PHI, &dphi, &Kphi, st));
-    struct Free2 {
-        PStep *a, *b;
-        ~Free2() {
-            dev_free(a);
-            dev_free(b);
-        }
-    } fp{dphi, nullptr};
-    PP_TRY(upload_programs(B, polys, PP_APPLY_P, &dp, &Kp, st));
-    fp.b = dp;
+    BatchProg phi, pol;
+    PP_TRY(upload_programs(B, polys, PP_APPLY_PHI, phi, st));
+    PP_TRY(upload_programs(B, polys, PP_APPLY_P, pol, st));
     std::vector<pp_info> inf(P);
     for (auto &i : inf) {
         std::memset(&i, 0, sizeof(i));
@@ -1125,14 +1342,14 @@ pp_status pp_batch_solve(pp_batch B, const pp_poly *polys, int nrhs, const doubl
         for (int j = c * seg; j < std::min(m, (c + 1) * seg); ++j) {
             if (delayed) {
                 // phi(A) of the pending vector; its column completes one step later
-                PP_TRY(run_bprog(B, pr, R, dphi, Kphi, w.P(3), bcol(w, pr, j + 1), w, st, true));
+                PP_TRY(run_bprog(B, pr, R, phi, w.P(3), bcol(w, pr, j + 1), w, st, true));
                 PP_TRY(bdcgs(B, pr, R, w, j, false, st));
                 if (j >= 1)
                     HIP_TRY(launch_bgivens_step(G, j - 1, B->dH + (size_t)(j - 1) * (m + 1), m * (m + 1),
                                                 kBreakdownTolB, st));
                 continue;
             }
-            PP_TRY(run_bprog(B, pr, R, dphi, Kphi, bcol(w, pr, j), bcol(w, pr, j + 1), w, st, true));
+            PP_TRY(run_bprog(B, pr, R, phi, bcol(w, pr, j), bcol(w, pr, j + 1), w, st, true));
             PP_TRY(bcgs2(B, pr, R, w, j, B->Hc, B->ldh, st, true));
             HIP_TRY(launch_bgivens_step(G, j, B->Hc, B->ldh, kBreakdownTolB, st));
         }
@@ -1150,7 +1367,7 @@ pp_status pp_batch_solve(pp_batch B, const pp_poly *polys, int nrhs, const doubl
         }
         HIP_TRY(launch_bgivens_solve(G, B->z, B->ldh, st));
         HIP_TRY(launch_bcombine(bl, pr, R, w.V, w.ldv, B->kdev, B->z, B->ldh, w.P(3), st));
-        PP_TRY(run_bprog(B, pr, R, dp, Kp, w.P(3), w.P(4), w, st));
+        PP_TRY(run_bprog(B, pr, R, pol, w.P(3), w.P(4), w, st));
         HIP_TRY(launch_axpy_x(pr, (int)nR, 1.0, w.P(4), x, st));
         {
             const BWork &w64 = B->ws[0].V ? B->ws[0] : w;
@@ -1218,6 +1435,8 @@ pp_status pp_batch_solve(pp_batch B, const pp_poly *polys, int nrhs, const doubl
             PP_TRY(B->ensure(0, m, R));
             if (!B->cfg[0][R].tuned) PP_TRY(tune_bchain(B, 0, R, st));
         }
+        PP_TRY(upload_segments(B, polys, PP_APPLY_PHI, prec, R, phi, st));
+        PP_TRY(upload_segments(B, polys, PP_APPLY_P, prec, R, pol, st));
         const double eta = (prec != PP_F64 && opts->inner_eta > 0.0) ? opts->inner_eta : kInnerEtaB[prec];
         // per-pair inputs of the cycle: beta, the inner target, 1/beta (0 for
         // pairs that are done) and the run flags

@@ -10,6 +10,7 @@
 
 #include <cstdint>
 
+#include "grid2.h"
 #include "kernels.h"
 
 namespace ppg {
@@ -67,6 +68,36 @@ struct BatchBlocks {
 // temporary (each n_total*R elements of the precision's type).
 hipError_t launch_bchain(const BatchSell &S, int prec, int R, const PStep *desc, int K, int k, void *const bufs[5],
                          hipStream_t st);
+// Many chain steps per launch on the box copy (FP64 and FP32 vectors): every
+// system's grid is cut into tiles {system, first column, first row, 0} that
+// stay exact over `steps` steps in regions of 64 x waves ry points, and its
+// chain program into segments of at most `steps` steps. Launches with an
+// accumulator have tiles of their own: its registers may leave room for
+// fewer waves (acc_waves).
+struct BatchGrid {
+    const int4 *tile = nullptr, *acc_tile = nullptr;
+    int ntiles = 0, acc_ntiles = 0;
+    int ry = 0, waves = 0, acc_waves = 0, steps = 0;
+};
+// Segment l of a system's program: steps first .. first + count - 1 (count 0:
+// nothing) from buffer `in`; the last result to `out` (-1: not stored; fin:
+// input - result), the accumulator in buffer acc (-1: none; acc_init: it
+// starts at zero).
+struct BatchSeg {
+    int first, count, in, out, fin, acc, acc_init, pad;
+};
+// Waves per workgroup at most (0: not built): two vectors of ry R values a
+// lane, three with an accumulator, beside about 60 registers; 16 waves leave
+// a lane 128, 8 waves 256.
+constexpr int batch_grid_max_waves(size_t value_bytes, int R, int ry, bool acc) {
+    const size_t regs = value_bytes / 4 * (size_t)(R * ry) * (acc ? 3 : 2);
+    return regs <= 54 ? 16 : regs <= 96 ? 8 : 0;
+}
+bool batch_grid_ok(int prec, int R, int ry, int waves, int steps);
+// Launch l of L: segment l of every active system (segs: nsys x L); acc: the
+// programs have an accumulator.
+hipError_t launch_bgrid(const BatchSell &S, const BatchGrid &g, bool acc, int prec, int R, const PStep *desc, int K,
+                        const BatchSeg *segs, int L, int l, void *const bufs[5], hipStream_t st);
 // partial[b*ldp + c*R + r] = sum over block b of V_c[i*R+r] * w[i*R+r], c < ncols
 hipError_t launch_bdots(const BatchBlocks &B, int prec, int R, const void *V, long ldv, int ncols, const void *w,
                         double *partial, int ldp, hipStream_t st);

@@ -496,12 +496,14 @@ pp_status build_round_plan(pp_matrix A, int prec, int ept, int4 **dst, int *ndst
 }
 
 // The shapes of the 2-D multi-step kernel worth timing, the most promising
-// first by a model of one step's time: 4 us per launch (the launch and its
-// trip to memory) over its steps, then per step 0.12 us for the barrier and
-// the issue time of the region's operations on the fullest CU.
+// first by a model of one step's time fitted to a sweep of all shapes (50^2 to
+// 1024^2; its four best always held one within 3 % of the fastest): 4.6 us a
+// launch over its steps, then per wave of the fullest CU's SIMDs a fixed
+// part and a part per point of a lane.
 void grid2_shapes(const Grid2Mat &m, int prec, std::vector<Grid2Shape> &out) {
     std::vector<std::pair<double, Grid2Shape>> all;
-    const double ops = (m.nd == 13 ? 15.0 : 7.0) + (prec == 0 ? (m.nd == 13 ? 18.0 : 3.0) : 1.0);
+    const double fixed = m.nd == 13 ? 0.1 : 0.0, wave = prec == 0 ? 0.05 : 0.025;
+    const double point = m.nd == 13 ? (prec == 0 ? 0.045 : 0.036) : (prec == 0 ? 0.024 : 0.017);
     for (int vx = 1; vx <= 2; ++vx)
         for (int ry = 1; ry <= kGrid2MaxRows; ++ry) {
             if (!grid2_built(m, prec, vx, ry)) continue;
@@ -518,7 +520,7 @@ void grid2_shapes(const Grid2Mat &m, int prec, std::vector<Grid2Shape> &out) {
                     long tiles;
                     if (!grid2_tiles(m, s, n, &tx, &ty, &tiles)) break;
                     const double per_simd = (double)((tiles + 255) / 256) * std::max(1.0, waves / 4.0);
-                    const double t = 4.0 / n + 0.12 + per_simd * ry * vx * ops * 4.0 / 2400.0;
+                    const double t = 4.6 / n + fixed + per_simd * (wave + point * ry * vx);
                     if (t < bt) {
                         bt = t;
                         best = s;
@@ -874,24 +876,6 @@ int march_group_len(const std::vector<Step> &prog, size_t i, int smax) {
     return g;
 }
 
-// A chain program that is one chain: each step one sparse product of the
-// previous step's result (the first step's of the input), with at most the
-// previous step's input as aux, one accumulator that every step updates and
-// the first initialises (or none), and a final vector on the last step only.
-bool linear_program(const std::vector<Step> &prog) {
-    for (size_t i = 0; i < prog.size(); ++i) {
-        const Step &s = prog[i];
-        const bool last = i + 1 == prog.size();
-        if (s.spmv != 1 || s.in != (i ? prog[i - 1].out : (int)B_IN)) return false;
-        if (s.aux != B_NONE && (i == 0 || s.aux != prog[i - 1].in)) return false;
-        if (last ? s.out != B_NONE && s.out != B_OUT : s.out < B_P0) return false;
-        if (s.fin && !(last && s.out == B_OUT)) return false;
-        if (s.acc != prog[0].acc || (s.acc != B_NONE && (s.acc_init != 0) != (i == 0))) return false;
-    }
-    if (prog.empty() || prog[0].acc == B_NONE) return !prog.empty();
-    return prog[0].acc == B_OUT && prog.back().out == B_NONE && !prog.back().fin;
-}
-
 // One launch of a chain program as run_program issues it.
 struct Planned {
     int kind;   // 0: one step, 1: the two-step pair kernel, 2: the marching kernel, 3: the 2-D multi-step kernel
@@ -908,16 +892,11 @@ struct Planned {
 void plan_program(pp_matrix A, const std::vector<Step> &prog, int prec, std::vector<Planned> &out) {
     out.clear();
     if (A->g2[prec].steps > 0 && !A->persist[prec] && linear_program(prog)) {
-        // launches of about equal length, none between a pair's two steps;
-        // each reads what the one before it wrote, two temporaries in turn
-        const int N = (int)prog.size(), smax = A->g2[prec].steps;
-        const int per = (N + (N + smax - 1) / smax - 1) / ((N + smax - 1) / smax);
-        int to = B_P0;
-        for (int i = 0; i < N;) {
-            int g = std::min(per, N - i);
-            if (i + g < N && prog[i + g].aux != B_NONE) g += g < smax ? 1 : -1;
-            const bool last = i + g == N;
-            out.push_back(Planned{3, i, g, last ? prog[N - 1].out : to, -1});
+        // each launch reads what the one before it wrote, two temporaries in turn
+        int i = 0, to = B_P0;
+        for (int g : split_program(prog, A->g2[prec].steps)) {
+            const bool last = i + g == (int)prog.size();
+            out.push_back(Planned{3, i, g, last ? prog.back().out : to, -1});
             to = to == B_P0 ? B_P1 : B_P0;
             i += g;
         }

@@ -69,7 +69,8 @@ __global__ __launch_bounds__(1024) void k_grid2(G2Args<AT> a) {
     const int x0 = (t % a.ntx) * a.tx, y0 = (t / a.ntx) * a.ty;  // the tile
     const int x = x0 - a.hx + lane * VX, yw = y0 - a.hy + wave * RY;
     const bool all = x0 - a.hx >= 0 && x0 - a.hx + 64 * VX <= gx && y0 - a.hy >= 0 && y0 - a.hy + waves * RY <= gy;
-    typename G::Rows A, B, acc;
+    typename G::Rows A, B;
+    typename G::AccRows acc;
     typename G::Coef cf;
     typename G::Live live;
     Grid2Step<AT> mine = a.steps[min(lane, a.n - 1)];
@@ -148,17 +149,17 @@ hipError_t g2_launch(const G2Args<AT> &a, const Grid2Shape &s, hipStream_t st) {
 // two of 2, 3 or 4. One row a wave pays the barrier for too little work and
 // 12 or 16 points a lane (8 waves, their registers) gain nothing: at 1024^2 in FP64
 // 1.41 us a step with 2 x 4, 1.49 with 2 x 8. Per-row coefficients stay in
-// registers, 5 a point, so two columns stop at 2 rows.
+// registers, 5 a point, so those stop at 4 points a lane.
 template <typename AT, int ND, bool VAR>
 hipError_t g2_shape(const G2Args<AT> &a, const Grid2Shape &s, hipStream_t st) {
     switch (s.vx * 10 + s.ry) {
         case 12: return g2_launch<AT, ND, VAR, 1, 2>(a, s, st);
         case 13: return g2_launch<AT, ND, VAR, 1, 3>(a, s, st);
         case 14: return g2_launch<AT, ND, VAR, 1, 4>(a, s, st);
-        case 16: return g2_launch<AT, ND, VAR, 1, 6>(a, s, st);
         case 22: return g2_launch<AT, ND, VAR, 2, 2>(a, s, st);
     }
     if constexpr (!VAR) {
+        if (s.vx == 1 && s.ry == 6) return g2_launch<AT, ND, VAR, 1, 6>(a, s, st);
         if (s.vx == 2 && s.ry == 3) return g2_launch<AT, ND, VAR, 2, 3>(a, s, st);
         if (s.vx == 2 && s.ry == 4) return g2_launch<AT, ND, VAR, 2, 4>(a, s, st);
     }
@@ -207,7 +208,8 @@ hipError_t g2_run(const Grid2Mat &m, const AT *coef, const AT *dval, const Grid2
 
 bool grid2_built(const Grid2Mat &m, int prec, int vx, int ry) {
     if ((prec != 0 && prec != 1) || !((m.nd == 5 && (m.constant() || m.dval64)) || (m.nd == 13 && m.constant()))) return false;
-    return (vx == 1 && (ry == 2 || ry == 3 || ry == 4 || ry == 6)) || (vx == 2 && (ry == 2 || (m.constant() && (ry == 3 || ry == 4))));
+    if (vx * ry > 4 && !m.constant()) return false;
+    return (vx == 1 && (ry == 2 || ry == 3 || ry == 4 || ry == 6)) || (vx == 2 && (ry == 2 || ry == 3 || ry == 4));
 }
 
 bool grid2_tiles(const Grid2Mat &m, const Grid2Shape &s, int n, int *tx, int *ty, long *tiles) {

@@ -62,7 +62,10 @@ __device__ __forceinline__ void loaded(double &v) { asm volatile("" : "+v"(v)); 
 // ND 5: the stencil of the diagonals -g, -1, 0, 1, g; ND 13: of -2g, -g-1,
 // -g, -g+1, -2, -1, 0, 1, 2, g-1, g, g+1, 2g. VAR: the coefficients are the
 // lane's own (per point); otherwise one set for all points.
-template <typename AT, int ND, bool VAR, int VX, int NC, int RY>
+//
+// WITH_ACC: launches may have an accumulator or a final vector, which is one
+// more value a point in registers (acc); without it acc is not touched.
+template <typename AT, int ND, bool VAR, int VX, int NC, int RY, bool WITH_ACC = true>
 struct Grid2 {
     static_assert(ND == 5 || ND == 13, "5- or 13-point stencils");
     static constexpr int RHO = ND == 13 ? 2 : 1;
@@ -71,6 +74,7 @@ struct Grid2 {
     static_assert(RY >= RHO, "a wave's edge rows are its own");
     static constexpr int NCOEF = VAR ? RY * VX : 1;
     typedef AT Rows[RY][NV];
+    typedef AT AccRows[WITH_ACC ? RY : 1][WITH_ACC ? NV : 1];
     typedef AT Coef[NCOEF][ND];
     typedef bool Live[RY][VX];
 
@@ -107,7 +111,7 @@ struct Grid2 {
     // arithmetic on both sides and a select: 27 operations a point in FP64
     // instead of 10.
     template <bool MASK, bool ACC, int KIND>
-    static __device__ __forceinline__ void row(int r, const Rows &S, Rows &D, Rows &acc, const Grid2Step<AT> &s,
+    static __device__ __forceinline__ void row(int r, const Rows &S, Rows &D, AccRows &acc, const Grid2Step<AT> &s,
                                                const Coef &cf, const AT (&up)[RHO][NV], const AT (&dn)[RHO][NV],
                                                const Live &live) {
         const AT(&m1)[NV] = r >= 1 ? S[r >= 1 ? r - 1 : 0] : up[RHO - 1];
@@ -151,7 +155,7 @@ struct Grid2 {
     // none of the neighbouring waves' are computed between the edge rows' way
     // into LDS and the barrier.
     template <bool MASK, bool ACC, int KIND>
-    static __device__ __forceinline__ void step(const Rows &S, Rows &D, Rows &acc, const Grid2Step<AT> &s,
+    static __device__ __forceinline__ void step(const Rows &S, Rows &D, AccRows &acc, const Grid2Step<AT> &s,
                                                 const Coef &cf, AT *edge, int wave, int waves, int lane,
                                                 const Live &live) {
 #pragma unroll
@@ -185,7 +189,7 @@ struct Grid2 {
     }
 
     template <bool MASK, bool ACC>
-    static __device__ __forceinline__ void any_step(const Rows &S, Rows &D, Rows &acc, const Grid2Step<AT> &s,
+    static __device__ __forceinline__ void any_step(const Rows &S, Rows &D, AccRows &acc, const Grid2Step<AT> &s,
                                                     const Coef &cf, AT *edge, int wave, int waves, int lane,
                                                     const Live &live) {
         if (s.flags & kG2Aux)
@@ -201,7 +205,7 @@ struct Grid2 {
     // holds step k (every wave has its own copy: a lane read costs a few
     // cycles, a scalar load a memory round trip on every step's critical path).
     template <bool MASK, bool ACC>
-    static __device__ __forceinline__ void run(Rows &A, Rows &B, Rows &acc, int n, const Grid2Step<AT> &mine,
+    static __device__ __forceinline__ void run(Rows &A, Rows &B, AccRows &acc, int n, const Grid2Step<AT> &mine,
                                                const Coef &cf, AT *lds, int wave, int waves, int lane,
                                                const Live &live) {
         AT *e1 = lds + (size_t)waves * NSLOT * NV * 64;
@@ -220,20 +224,22 @@ struct Grid2 {
     }
 
     // all: every point of the region lies inside the grid
-    static __device__ __forceinline__ void run_any(Rows &A, Rows &B, Rows &acc, int n, const Grid2Step<AT> &mine,
+    static __device__ __forceinline__ void run_any(Rows &A, Rows &B, AccRows &acc, int n, const Grid2Step<AT> &mine,
                                                    const Coef &cf, AT *lds, int wave, int waves, int lane, bool all,
                                                    bool with_acc, const Live &live) {
-        if (with_acc) {
-            if (all)
-                run<false, true>(A, B, acc, n, mine, cf, lds, wave, waves, lane, live);
-            else
-                run<true, true>(A, B, acc, n, mine, cf, lds, wave, waves, lane, live);
-        } else {
-            if (all)
-                run<false, false>(A, B, acc, n, mine, cf, lds, wave, waves, lane, live);
-            else
-                run<true, false>(A, B, acc, n, mine, cf, lds, wave, waves, lane, live);
+        if constexpr (WITH_ACC) {
+            if (with_acc) {
+                if (all)
+                    run<false, true>(A, B, acc, n, mine, cf, lds, wave, waves, lane, live);
+                else
+                    run<true, true>(A, B, acc, n, mine, cf, lds, wave, waves, lane, live);
+                return;
+            }
         }
+        if (all)
+            run<false, false>(A, B, acc, n, mine, cf, lds, wave, waves, lane, live);
+        else
+            run<true, false>(A, B, acc, n, mine, cf, lds, wave, waves, lane, live);
     }
 };
 

@@ -2,6 +2,7 @@
 // pi(A)v (Algorithm 1) or p(A)v (Algorithm 3) for an ordered root list.
 #include "poly.h"
 
+#include <algorithm>
 #include <atomic>
 
 namespace ppg {
@@ -99,6 +100,32 @@ std::vector<Step> program_p(const std::vector<Unit> &units) {
         first = 0;
     }
     return prog;
+}
+
+bool linear_program(const std::vector<Step> &prog) {
+    for (size_t i = 0; i < prog.size(); ++i) {
+        const Step &s = prog[i];
+        const bool last = i + 1 == prog.size();
+        if (s.spmv != 1 || s.in != (i ? prog[i - 1].out : (int)B_IN)) return false;
+        if (s.aux != B_NONE && (i == 0 || s.aux != prog[i - 1].in)) return false;
+        if (last ? s.out != B_NONE && s.out != B_OUT : s.out < B_P0) return false;
+        if (s.fin && !(last && s.out == B_OUT)) return false;
+        if (s.acc != prog[0].acc || (s.acc != B_NONE && (s.acc_init != 0) != (i == 0))) return false;
+    }
+    if (prog.empty() || prog[0].acc == B_NONE) return !prog.empty();
+    return prog[0].acc == B_OUT && prog.back().out == B_NONE && !prog.back().fin;
+}
+
+std::vector<int> split_program(const std::vector<Step> &prog, int smax) {
+    const int N = (int)prog.size(), launches = (N + smax - 1) / smax, per = (N + launches - 1) / launches;
+    std::vector<int> lens;
+    for (int i = 0; i < N;) {
+        int g = std::min(per, N - i);
+        if (i + g < N && prog[i + g].aux != B_NONE) g += g < smax ? 1 : -1;
+        lens.push_back(g);
+        i += g;
+    }
+    return lens;
 }
 
 }  // namespace ppg

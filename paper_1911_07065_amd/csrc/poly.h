@@ -32,6 +32,15 @@ std::vector<Step> program_phi(const std::vector<Unit> &units, bool want_pi);
 // contribution is folded into the step before it. Result lands in B_OUT.
 std::vector<Step> program_p(const std::vector<Unit> &units);
 
+// A chain program that is one chain: each step one sparse product of the
+// previous step's result (the first step's of the input), with at most the
+// previous step's input as aux, one accumulator that every step updates and
+// the first initialises (or none), and a final vector on the last step only.
+bool linear_program(const std::vector<Step> &prog);
+// Lengths (at most smax >= 2, about equal) of the launches a linear program
+// is cut into, none between a pair's two steps.
+std::vector<int> split_program(const std::vector<Step> &prog, int smax);
+
 }  // namespace ppg
 
 struct pp_poly_s {

@@ -47,8 +47,9 @@ CASES = {
     "bihar_40": (lambda: biharmonic2d(40), 13, True),
     "bihar_81": (lambda: biharmonic2d(81), 13, True),
 }
-ONE = [(1, 2), (1, 3), (1, 4), (1, 6), (2, 2)]
-SHAPES = {(5, True): ONE + [(2, 3), (2, 4)], (5, False): ONE, (13, True): ONE + [(2, 3), (2, 4)]}
+ONE = [(1, 2), (1, 3), (1, 4), (2, 2)]
+MORE = ONE + [(1, 6), (2, 3), (2, 4)]
+SHAPES = {(5, True): MORE, (5, False): ONE, (13, True): MORE}
 
 
 def _roots(nd):
