@@ -703,13 +703,24 @@ __device__ __forceinline__ void bvh_row(const XT *__restrict__ V, long ldv, int 
     }
 }
 
+// Per-system sums of the blocks' partial sums, in block order. A thread's
+// loads go out eight blocks at a time: taken one by one each waits a memory
+// round trip (a 256^2 system has 64 blocks: 24 us before, 6 us now).
 __global__ __launch_bounds__(256) void k_bred(const int32_t *boff, int R, const double *partial, int ldp, int nt,
                                               double *h, int ldh, double *H, long pstride, int hmode) {
     const int s = blockIdx.x;
     const int b0 = boff[s], b1 = boff[s + 1];
     for (int t = threadIdx.x; t < nt; t += 256) {
         double acc = 0.0;
-        for (int b = b0; b < b1; ++b) acc += partial[(long)b * ldp + t];
+        int b = b0;
+        for (; b + 8 <= b1; b += 8) {
+            double v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = partial[(long)(b + q) * ldp + t];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc += v[q];
+        }
+        for (; b < b1; ++b) acc += partial[(long)b * ldp + t];
         if (h) h[(long)s * ldh + t] = acc;
         if (H) {
             double *dst = H + ((long)s * R + t % R) * pstride + t / R;
@@ -1338,10 +1349,10 @@ hipError_t launch_bcombine(const BatchBlocks &B, int prec, int R, const void *V,
 }
 
 // ---------------------------------------------------------------------------
-// Givens least squares of every pair, on the device: one thread per system
-// runs its R pairs in order. The arithmetic is the host's GivensLS step for
-// step (multiply-adds not contracted), so a cycle decides exactly as the
-// host would.
+// Givens least squares of every pair, on the device: one wave per system,
+// lane r runs pair r. The arithmetic is the host's GivensLS step for step
+// (multiply-adds not contracted), so a cycle decides exactly as the host
+// would.
 // ---------------------------------------------------------------------------
 namespace {
 
@@ -1360,69 +1371,152 @@ __global__ __launch_bounds__(256) void k_bgivens_init(BGivens G, const double *b
     G.act[s] = a;
 }
 
-__global__ __launch_bounds__(256) void k_bgivens_step(BGivens G, int j, const double *Hc, int ldh, double tol_brk) {
+// What bounds it: the serial chain of j rotations. The column, the rotations
+// and the rotated column pass through LDS 64 entries at a time, loaded and
+// stored by the whole wave, so only the chain itself is serial: a thread
+// that read and wrote them in memory took 44 us at 48 systems x 4 (j about
+// 30), this 5 us.
+constexpr int kGivensChunk = 64;
+__global__ __launch_bounds__(64) void k_bgivens_step(BGivens G, int j, const double *Hc, int ldh, double tol_brk) {
 #pragma clang fp contract(off)
-    const int s = (int)(blockIdx.x * 256 + threadIdx.x);
-    if (s >= G.nsys) return;
-    const int m = G.m, ld = m + 1;
-    int a = 0;
-    for (int r = 0; r < G.R; ++r) {
-        const int p = s * G.R + r;
-        if (!G.run[p]) continue;
-        const double *h = Hc + (size_t)p * ldh;
-        G.steps[p] += 1;
-        bool finite = true;
-        double f = G.fro2[p];
-        for (int i = 0; i <= j + 1; ++i) {
-            finite = finite && isfinite(h[i]);
-            f += h[i] * h[i];
-        }
-        G.fro2[p] = f;
-        if (!finite) {
-            G.run[p] = 0;
-            continue;
-        }
-        double *col = G.Rm + (size_t)p * ld * m + (size_t)j * ld;
-        double *c = G.c + (size_t)p * m, *sn = G.s + (size_t)p * m, *g = G.g + (size_t)p * ld;
-        for (int i = 0; i <= j + 1; ++i) col[i] = h[i];
-        for (int i = 0; i < j; ++i) {
-            const double t1 = c[i] * col[i] + sn[i] * col[i + 1];
-            const double t2 = -sn[i] * col[i] + c[i] * col[i + 1];
-            col[i] = t1;
-            col[i + 1] = t2;
-        }
-        const double x = col[j], y = col[j + 1];
-        double cj, sj;
-        if (y == 0.0) {
-            cj = 1.0;
-            sj = 0.0;
-        } else if (fabs(y) > fabs(x)) {
-            const double tau = x / y;
-            sj = 1.0 / sqrt(1.0 + tau * tau);
-            cj = sj * tau;
-        } else {
-            const double tau = y / x;
-            cj = 1.0 / sqrt(1.0 + tau * tau);
-            sj = cj * tau;
-        }
-        c[j] = cj;
-        sn[j] = sj;
-        col[j] = cj * x + sj * y;
-        col[j + 1] = 0.0;
-        g[j + 1] = -sj * g[j];
-        g[j] = cj * g[j];
-        G.k[p] = j + 1;
-        const double sc = fabs(g[j + 1]);
-        G.sc[p] = sc;
-        if (h[j + 1] <= tol_brk * sqrt(f) || sc <= G.target[p])
-            G.run[p] = 0;
-        else
-            a = 1;
+    constexpr int RM = 4;  // right-hand sides at most
+    __shared__ double hs[RM][kGivensChunk + 1], cs[RM][kGivensChunk + 1], ss[RM][kGivensChunk + 1];
+    const int s = blockIdx.x, lane = threadIdx.x;
+    const int m = G.m, ld = m + 1, R = G.R, p = s * R + lane;
+    const bool mine = lane < R && G.run[p];
+    if (!__any(mine)) {  // every pair of the system has stopped
+        if (lane == 0) G.act[s] = 0;
+        return;
     }
-    G.act[s] = a;
+    double f = 0.0, x = 0.0;
+    bool finite = true;
+    if (mine) f = G.fro2[p];
+    for (int i0 = 0; i0 <= j; i0 += kGivensChunk) {
+        // entry i0 + lane of the column, rotation i0 + lane - 1
+        const int i = i0 + lane;
+        for (int r = 0; r < R; ++r) {
+            const size_t q = (size_t)s * R + r;
+            if (i <= j) hs[r][lane] = Hc[q * ldh + i];
+            if (i >= 1 && i <= j) {
+                cs[r][lane] = G.c[q * m + i - 1];
+                ss[r][lane] = G.s[q * m + i - 1];
+            }
+        }
+        __syncthreads();
+        if (mine) {
+            const int n = min(kGivensChunk, j + 1 - i0);
+#pragma unroll 4
+            for (int k = 0; k < n; ++k) {
+                const double h = hs[lane][k];
+                finite = finite && isfinite(h);
+                f += h * h;
+                if (i0 + k == 0) {
+                    x = h;
+                    continue;
+                }
+                const double c = cs[lane][k], sn = ss[lane][k];
+                const double t1 = c * x + sn * h, t2 = -sn * x + c * h;
+                hs[lane][k] = t1;  // entry i0 + k - 1 of the rotated column
+                x = t2;
+            }
+        }
+        __syncthreads();
+        for (int r = 0; r < R; ++r)
+            if (i >= 1 && i <= j) G.Rm[((size_t)s * R + r) * ld * m + (size_t)j * ld + i - 1] = hs[r][lane];
+        __syncthreads();
+    }
+    bool run = false;
+    if (mine) {
+        const double y = Hc[(size_t)p * ldh + j + 1];
+        finite = finite && isfinite(y);
+        f += y * y;
+        G.steps[p] += 1;
+        G.fro2[p] = f;
+        if (finite) {
+            double *col = G.Rm + (size_t)p * ld * m + (size_t)j * ld;
+            double *c = G.c + (size_t)p * m, *sn = G.s + (size_t)p * m, *g = G.g + (size_t)p * ld;
+            double cj, sj;
+            if (y == 0.0) {
+                cj = 1.0;
+                sj = 0.0;
+            } else if (fabs(y) > fabs(x)) {
+                const double tau = x / y;
+                sj = 1.0 / sqrt(1.0 + tau * tau);
+                cj = sj * tau;
+            } else {
+                const double tau = y / x;
+                cj = 1.0 / sqrt(1.0 + tau * tau);
+                sj = cj * tau;
+            }
+            c[j] = cj;
+            sn[j] = sj;
+            col[j] = cj * x + sj * y;
+            col[j + 1] = 0.0;
+            const double gj = g[j];
+            g[j + 1] = -sj * gj;
+            g[j] = cj * gj;
+            G.k[p] = j + 1;
+            const double sc = fabs(-sj * gj);
+            G.sc[p] = sc;
+            run = !(y <= tol_brk * sqrt(f) || sc <= G.target[p]);
+        }
+        G.run[p] = run ? 1 : 0;
+    }
+    const bool any = __any(run);
+    if (lane == 0) G.act[s] = any ? 1 : 0;
 }
 
-__global__ __launch_bounds__(256) void k_bgivens_solve(BGivens G, double *z, int ldz) {
+// Back substitution R z = g, one wave per pair: lane i holds the rows i + 64 q
+// (q < NQ) of the running right-hand side, columns from the last to the
+// first, eight columns' loads at a time. A thread per pair took 205 us for
+// 192 pairs of about 35 columns, one load after the other; this 12 us.
+template <int NQ>
+__global__ __launch_bounds__(64) void k_bgivens_solve(BGivens G, double *z, int ldz) {
+#pragma clang fp contract(off)
+    const int p = blockIdx.x, lane = threadIdx.x;
+    const int k = G.k[p], ld = G.m + 1;
+    const double *Rm = G.Rm + (size_t)p * ld * G.m, *g = G.g + (size_t)p * ld;
+    double t[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) t[q] = lane + 64 * q < k ? g[lane + 64 * q] : 0.0;
+    for (int c1 = k; c1 > 0; c1 -= 8) {
+        double col[8][NQ];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int c = c1 - 1 - u;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int i = lane + 64 * q;
+                col[u][q] = c >= 0 && i <= c ? Rm[(size_t)i + (size_t)c * ld] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int c = c1 - 1 - u;
+            if (c < 0) break;
+            double num = 0.0, den = 1.0;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+                if (c / 64 == q) {
+                    num = __shfl(t[q], c % 64);
+                    den = __shfl(col[u][q], c % 64);
+                }
+            const double zc = num / den;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int i = lane + 64 * q;
+                if (i < c) t[q] -= col[u][q] * zc;
+                if (i == c) t[q] = zc;
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        if (lane + 64 * q < k) z[(size_t)p * ldz + lane + 64 * q] = t[q];
+}
+
+// The same for more columns than k_bgivens_solve's lanes hold: one thread per pair.
+__global__ __launch_bounds__(256) void k_bgivens_solve_long(BGivens G, double *z, int ldz) {
 #pragma clang fp contract(off)
     const int p = (int)(blockIdx.x * 256 + threadIdx.x);
     if (p >= G.nsys * G.R) return;
@@ -1463,8 +1557,8 @@ hipError_t launch_bgivens_init(const BGivens &G, const double *beta, hipStream_t
 
 hipError_t launch_bgivens_step(const BGivens &G, int j, const double *Hc, int ldh, double tol_brk, hipStream_t st) {
     if (G.nsys <= 0) return hipSuccess;
-    if (j < 0 || j >= G.m || ldh < j + 2) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_bgivens_step, dim3((G.nsys + 255) / 256), dim3(256), 0, st, G, j, Hc, ldh, tol_brk);
+    if (j < 0 || j >= G.m || ldh < j + 2 || G.R < 1 || G.R > 4) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_bgivens_step, dim3(G.nsys), dim3(64), 0, st, G, j, Hc, ldh, tol_brk);
     return hipGetLastError();
 }
 
@@ -1472,7 +1566,13 @@ hipError_t launch_bgivens_solve(const BGivens &G, double *z, int ldz, hipStream_
     const int P = G.nsys * G.R;
     if (P <= 0) return hipSuccess;
     if (ldz < G.m) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_bgivens_solve, dim3((P + 255) / 256), dim3(256), 0, st, G, z, ldz);
+    // a lane's rows of eight columns stay in registers: 4 rows a lane at most
+    if (G.m <= 64)
+        hipLaunchKernelGGL(k_bgivens_solve<1>, dim3(P), dim3(64), 0, st, G, z, ldz);
+    else if (G.m <= 256)
+        hipLaunchKernelGGL(k_bgivens_solve<4>, dim3(P), dim3(64), 0, st, G, z, ldz);
+    else
+        hipLaunchKernelGGL(k_bgivens_solve_long, dim3((P + 255) / 256), dim3(256), 0, st, G, z, ldz);
     return hipGetLastError();
 }
 
