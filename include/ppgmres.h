@@ -158,7 +158,7 @@ void pp_matrix_destroy(pp_matrix A);
 pp_status pp_matrix_tune(pp_matrix A, int prec, void *stream, int *variant, int *remap,
                          double *us_per_launch);
 
-/* Force a chain-step variant (0 <= variant < 34, remap 0/1; 15 = persistent) for a precision
+/* Force a chain-step variant (0 <= variant < 35, remap 0/1; 15 = persistent) for a precision
  * instead of tuning, e.g. to test every variant. Variant 31 (box) applies to a
  * constant-coefficient 5- or 7-point box stencil (see pp_matrix_march's
  * `constant`) whose grid lines hold a multiple of 4 points: it reads no
@@ -170,7 +170,14 @@ pp_status pp_matrix_tune(pp_matrix A, int prec, void *stream, int *variant, int 
  * each (block, band) tile's entries sorted by column so that a wave's
  * gathers share cache lines; a second launch adds, per row, the diagonal
  * product and the 4 (csort4) or 2 (csort2) partial sums in band order, then
- * finishes the step. PP_EINVAL when the copy is absent. */
+ * finishes the step. PP_EINVAL when the copy is absent.
+ * Variant 34 (ldsband) holds a band of the input in LDS per workgroup and
+ * gathers there; a second launch adds the (at most 8) bands' sums per row
+ * in band order and finishes the step. Its copy is built by the tuner or by
+ * this call for matrices of at least 4096 rows without a diagonal-format
+ * copy whose vector is at most 8 bands of 128 KB (65536 columns in
+ * bfloat16) and whose rows hold at most 127 entries per band; PP_EINVAL
+ * elsewhere. */
 pp_status pp_matrix_set_variant(pp_matrix A, int prec, int variant, int remap);
 
 /* The chain-step variant in use for a precision, without tuning: variant

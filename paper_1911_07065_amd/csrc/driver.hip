@@ -152,6 +152,8 @@ struct pp_matrix_s {
     float *cs_val32 = nullptr, *cs_dg32 = nullptr;
     int cs_nb = 0, cs_sb = 0, cs_W = 0, cs_maxe = 0;
     long cs_nnz = 0;
+    // column bands in LDS per precision (nb == 0: none; built by the tuner)
+    LBand lb[3];
     // pattern-coded diagonal copy (few distinct rows; dropped with the value codes)
     uint32_t *pcode = nullptr;
     uint8_t *pbyte = nullptr;
@@ -247,6 +249,7 @@ struct pp_matrix_s {
         d.cs_sb = cs_sb;
         d.cs_W = cs_W;
         d.cs_maxe = cs_maxe;
+        for (int p = 0; p < 3; ++p) d.lb[p] = lb[p];
         d.pcode = pcode;
         d.pbyte = pbyte;
         d.ptab64 = ptab64;
@@ -279,6 +282,16 @@ struct pp_matrix_s {
         dev_free(w.X);
         w.P1 = w.T = w.D = w.ACC = nullptr;
         w.m = -1;
+    }
+
+    static void free_lband(LBand &b) {
+        dev_free(b.sptr);
+        dev_free(b.perm);
+        dev_free(b.col);
+        dev_free(b.val);
+        dev_free(b.eperm);
+        dev_free(b.part);
+        b = LBand();
     }
 
     // The 5 extra vectors of a precision (after ensure_ws).
@@ -377,6 +390,7 @@ struct pp_matrix_s {
         dev_free(cs_dg64);
         dev_free(cs_dg32);
         dev_free(cs_part);
+        for (auto &b : lb) free_lband(b);
         dev_free(val_own);
         dev_free(scale);
         dev_free(sval64);
@@ -495,6 +509,49 @@ pp_status build_round_plan(pp_matrix A, int prec, int ept, int4 **dst, int *ndst
     return PP_OK;
 }
 
+// The copy with column bands in LDS for one precision (once): matrices whose
+// entries scatter, at least 4096 rows, whose vector is at most kLbMaxBands
+// bands. Leaves lb[prec].nb 0 where it does not apply.
+pp_status build_lband(pp_matrix A, int prec, hipStream_t st) {
+    if (A->lb[prec].nb > 0 || A->nnz == 0 || A->n < 4096 || !A->h_doff.empty()) return PP_OK;
+    LBand b;
+    b.nb = lb_bands(A->n, elem_size(prec), &b.W);
+    if (b.nb == 0) return PP_OK;
+    struct Guard {
+        LBand *b;
+        int *flag;
+        ~Guard() {
+            if (b) pp_matrix_s::free_lband(*b);
+            dev_free(flag);
+        }
+    } guard{&b, nullptr};
+    b.nwin = (A->n + kLbRows - 1) / kLbRows;
+    const size_t ns = (size_t)b.nb * b.nwin * (kLbRows / 64);
+    PP_TRY(dev_alloc(&b.sptr, ns + 1));
+    PP_TRY(dev_alloc(&b.perm, ns * 64));
+    PP_TRY(dev_alloc(&guard.flag, 1));
+    int res[2] = {0, 0};
+    HIP_TRY(hipMemsetAsync(guard.flag, 0, sizeof(int), st));
+    HIP_TRY(launch_lb_sort(A->n, A->rowptr, A->colind, b, guard.flag, st));
+    HIP_TRY(hipMemcpyAsync(&res[0], guard.flag, sizeof(int), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(&res[1], b.sptr + ns, sizeof(int), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    // no copy past three times the entries (a few long rows set their slices' width)
+    if (res[0] || res[1] <= 0 || 2 * (long)res[1] * 64 > 3L * A->nnz + 64L * (long)ns) return PP_OK;
+    b.pairs = res[1];
+    const size_t slots = ((size_t)b.pairs + kLbAhead) * 64;  // a slice's first pairs are read whatever its length
+    PP_TRY(dev_alloc(&b.col, slots));
+    PP_TRY(dev_alloc(&b.eperm, 2 * slots));
+    PP_TRY(dev_alloc((char **)&b.val, 2 * slots * (prec == PP_F64 ? 8 : 4)));
+    PP_TRY(dev_alloc((char **)&b.part, (size_t)b.nb * A->n * (prec == PP_F64 ? 8 : 4)));
+    HIP_TRY(launch_lb_fill(A->n, A->rowptr, A->colind, b, st));
+    HIP_TRY(launch_lb_values(b, prec == PP_F64, A->val, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    A->lb[prec] = b;
+    guard.b = nullptr;
+    return PP_OK;
+}
+
 // The shapes of the 2-D multi-step kernel worth timing, the most promising
 // first by a model of one step's time fitted to a sweep of all shapes (50^2 to
 // 1024^2; its four best always held one within 3 % of the fastest): 4.6 us a
@@ -575,6 +632,7 @@ pp_status tune_chain(pp_matrix A, int prec, hipStream_t st) {
     PP_TRY(A->ensure_ws(prec, 0));
     PP_TRY(build_round_plan(A, prec, 8, &A->tileB8[prec], &A->ntileB8[prec], st));
     PP_TRY(build_round_plan(A, prec, 16, &A->tileB16[prec], &A->ntileB16[prec], st));
+    PP_TRY(build_lband(A, prec, st));
     const Workspace &w = A->ws[prec];
     HIP_TRY(hipMemsetAsync(w.P0, 0, (size_t)w.ldv * elem_size(prec), st));
     HIP_TRY(hipMemsetAsync(w.P1, 0, (size_t)w.ldv * elem_size(prec), st));
@@ -605,7 +663,7 @@ pp_status tune_chain(pp_matrix A, int prec, hipStream_t st) {
             ((v == CV_SELLD || v == CV_SELLD4) && !A->sdel) || ((v == CV_DIA || v == CV_DIA4) && A->h_doff.empty()) ||
             (v == CV_DIAC && !A->dcode) || (v == CV_DIAP && !A->pcode) || (v == CV_DIAPV && !A->pbyte) ||
             (v == CV_BAND2 && A->bandK[0] == 0) || (v == CV_BAND4 && A->bandK[1] == 0) ||
-            ((v == CV_CSORT4 || v == CV_CSORT2) && A->cs_nb == 0) ||
+            ((v == CV_CSORT4 || v == CV_CSORT2) && A->cs_nb == 0) || (v == CV_LBAND && A->lb[prec].nb == 0) ||
             (v == CV_TILEB8 && A->ntileB8[prec] == 0) ||
             (v == CV_TILEB16 && A->ntileB16[prec] == 0) || (v == CV_BOX && !box_step_ok(A->dev())))
             continue;
@@ -1154,6 +1212,13 @@ int64_t format_bytes(pp_matrix A, int prec) {
             return (int64_t)A->cs_nnz * (sv + 4) + nt * (kCsRows + 1) * 2 + (nt + 1) * 4 +
                    (A->cs_dperm ? n * sv : 0) + 2 * nsb * n * sv;
         }
+        case CV_LBAND: {
+            // columns and values by pairs, permuted rows, slice offsets; the
+            // partial sums written and read
+            const LBand &b = A->lb[prec];
+            const int64_t ns = (int64_t)b.nb * b.nwin * (kLbRows / 64);
+            return (int64_t)b.pairs * 64 * (4 + 2 * sv) + ns * 64 * 2 + 4 * (ns + 1) + 2 * (int64_t)b.nb * n * sv;
+        }
         default:  // CSR: row tiles, lanes per row, persistent
             return nnz * (sv + 4) + 4 * (n + 1);
     }
@@ -1163,7 +1228,7 @@ int64_t format_bytes(pp_matrix A, int prec) {
 int64_t product_launches(pp_matrix A, int prec) {
     const int v = A->variant[prec];
     if (v == CV_BAND2 || v == CV_BAND4) return A->bandK[v == CV_BAND2 ? 0 : 1];
-    if (v == CV_CSORT4 || v == CV_CSORT2) return 2;
+    if (v == CV_CSORT4 || v == CV_CSORT2 || v == CV_LBAND) return 2;
     return 1;
 }
 
@@ -2079,6 +2144,8 @@ pp_status refresh_values(pp_matrix A, const double *val, hipStream_t st) {
         if (A->cs_nnz > 0) HIP_TRY(launch_sell_values(A->cs_nnz, A->cs_perm, val, A->cs_val64, A->cs_val32, st));
         if (A->cs_dperm) HIP_TRY(launch_sell_values(A->n, A->cs_dperm, val, A->cs_dg64, A->cs_dg32, st));
     }
+    for (int p = 0; p < 3; ++p)
+        if (A->lb[p].nb > 0) HIP_TRY(launch_lb_values(A->lb[p], p == PP_F64, val, st));
     if (A->dcode) {
         // the codes stay when every entry still equals its code's new value
         // (a constant-coefficient stencil with new coefficients); else drop
@@ -2446,6 +2513,15 @@ pp_status pp_matrix_set_variant(pp_matrix A, int prec, int variant, int remap) {
             set_error("pp_matrix_set_variant: no column-sorted copy (built only for matrices of at least 4096 rows "
                       "whose entries lie far from the diagonal, when every tile fits)");
             return PP_EINVAL;
+        }
+        if (variant == CV_LBAND) {
+            HIP_TRY(hipDeviceSynchronize());  // values set on another stream
+            PP_TRY(build_lband(A, prec, 0));
+            if (A->lb[prec].nb == 0) {
+                set_error("pp_matrix_set_variant: no column bands in LDS (built only for matrices of at least 4096 rows "
+                          "whose entries lie far from the diagonal and whose vector is at most 8 bands of 128 KB)");
+                return PP_EINVAL;
+            }
         }
         if ((variant == CV_DIAP && !A->pcode) || (variant == CV_DIAPV && !A->pbyte)) {
             set_error("pp_matrix_set_variant: no pattern-coded diagonal copy (no value-coded copy, too many "

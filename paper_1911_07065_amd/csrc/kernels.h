@@ -10,6 +10,8 @@
 #include <cstdint>
 #include <vector>
 
+#include "lband.h"
+
 namespace ppg {
 
 // chain-step kernel variants (the autotuner picks one per matrix and precision)
@@ -48,7 +50,8 @@ enum ChainVariant : int {
     CV_BOX = 31,      // constant-coefficient box stencil: no per-row matrix data, 4 points of a grid line per lane
     CV_CSORT4 = 32,   // column-sorted tiles of kCsRows rows x one column band, 4 partial sums per row
     CV_CSORT2 = 33,   // the same, 2 partial sums per row (twice the bands per workgroup)
-    CV_COUNT = 34
+    CV_LBAND = 34,    // column bands of the input held in LDS, the gathers there (lband.h)
+    CV_COUNT = 35
 };
 
 // A chain step as the persistent kernel reads it from device memory.
@@ -175,6 +178,7 @@ struct DevCSR {
     const float *cs_dg32;
     void *cs_part;
     int cs_nb, cs_sb, cs_W, cs_maxe;
+    LBand lb[3];  // per precision: column bands in LDS (nb == 0: absent)
     // box geometry (box_nd == 0: none): the rows are the points of a
     // box[0] x box[1] x box[2] grid, row x + box[0] (y + box[1] z), with
     // entries only on the diagonals 0, +-1, +-box[0] (and +-box[0] box[1]

@@ -1158,6 +1158,51 @@ __global__ __launch_bounds__(256) void k_chain_cs_finish(ChainArgs<VT, XT> a, co
     row_finish(a, r, s, p);
 }
 
+// The second launch of a product with its bands in LDS: a row's NB partial
+// sums in band order, then the step's update; every load goes out at once.
+template <typename VT, typename XT, int NB>
+__global__ __launch_bounds__(256) void k_chain_lb_finish(ChainArgs<VT, XT> a,
+                                                         const typename Arith<XT>::T *__restrict__ part) {
+    using AT = typename Arith<XT>::T;
+    const int r = blockIdx.x * 256 + threadIdx.x;
+    if (r >= a.n) return;
+    const RowPre<AT> p = row_prefetch(a, r);
+    AT t[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) t[k] = part[(size_t)k * a.n + r];
+    AT s = t[0];
+#pragma unroll
+    for (int k = 1; k < NB; ++k) s += t[k];
+    row_finish(a, r, s, p);
+}
+
+template <typename VT, typename XT>
+hipError_t lb_launch(const LBand &b, int prec, const ChainArgs<VT, XT> &a, int remap, hipStream_t st) {
+    using AT = typename Arith<XT>::T;
+    const hipError_t e = launch_lb_product(b, prec, a.n, a.in, remap, st);
+    if (e != hipSuccess) return e;
+    const dim3 g((a.n + 255) / 256);
+    const AT *part = (const AT *)b.part;
+    switch (b.nb) {
+#define PP_LB_NB(N)                                                                                      \
+    case N:                                                                                              \
+        hipLaunchKernelGGL((k_chain_lb_finish<VT, XT, N>), g, dim3(256), 0, st, a, part);                \
+        break;
+        PP_LB_NB(1)
+        PP_LB_NB(2)
+        PP_LB_NB(3)
+        PP_LB_NB(4)
+        PP_LB_NB(5)
+        PP_LB_NB(6)
+        PP_LB_NB(7)
+        PP_LB_NB(8)
+#undef PP_LB_NB
+        default:
+            return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 template <typename VT>
 const VT *cs_vals(const DevCSR &A);
 template <>
@@ -2220,6 +2265,8 @@ hipError_t chain_launch(const DevCSR &A, const VT *val, const StepPtrs &s, int v
             return cs_launch<VT, XT>(A, a, 4, remap, st);
         case CV_CSORT2:
             return cs_launch<VT, XT>(A, a, 2, remap, st);
+        case CV_LBAND:
+            return lb_launch<VT, XT>(A.lb[prec_of<XT>()], prec_of<XT>(), a, remap, st);
         case CV_TILEB8: {
             const int p = prec_of<XT>();
             if (A.ntileB8[p] == 0) return hipErrorInvalidValue;
@@ -3567,7 +3614,7 @@ const char *chain_variant_name(int v) {
                                           "tilev16x2", "vk2x4x4", "vk4x4x2", "vk8x4x1", "vk16x2x2", "persist8",
                                           "tileb8x1", "tileb16x2", "sell64", "sell64t", "sell64x2", "sell64x4", "sell64d16", "sell64d16x4",
                                               "dia2",   "dia1", "diac", "diap", "tile8b2", "tile8b4", "diapv", "box",
-                                          "csort4", "csort2"};
+                                          "csort4", "csort2", "ldsband"};
     return (v >= 0 && v < CV_COUNT) ? names[v] : "?";
 }
 
