@@ -27,7 +27,7 @@ HIP_FLAGS = [
 ]
 # the host core decides integer results (orderings, counts) from FP64
 # comparisons: no contraction, no fast-math
-HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wall"]
+HOST_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wall"]
 
 
 def _run(cmd):

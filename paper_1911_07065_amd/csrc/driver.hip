@@ -197,6 +197,16 @@ struct pp_matrix_s {
     double *small = nullptr;    // h1 | h2 | H | inv | z   (5 * ldp)
     double *hpin = nullptr;     // pinned host mirror (2 * ldp)
     double *r64 = nullptr, *t64 = nullptr;
+    double *hess = nullptr;  // Hessenberg matrix of a setup cycle (hess_len values, kept between setups)
+    size_t hess_len = 0;
+    pp_status ensure_hess(size_t len) {
+        if (hess_len >= len) return PP_OK;
+        dev_free(hess);
+        hess_len = 0;
+        PP_TRY(dev_alloc(&hess, len));
+        hess_len = len;
+        return PP_OK;
+    }
     int nblk_dot = 0, nblk_upd = 0, nblk_ud = 0;
 
     DevCSR dev() const {
@@ -408,6 +418,7 @@ struct pp_matrix_s {
         dev_free(npart);
         dev_free(small);
         dev_free(r64);
+        dev_free(hess);
         if (hpin) (void)hipHostFree(hpin);
     }
 };
@@ -2805,12 +2816,8 @@ pp_status setup_arnoldi(pp_matrix A, const double *v0, int d, hipStream_t st, st
     // stay in device memory and the host looks for a breakdown once at the
     // end (columns after a breakdown are discarded).
     const int ld = d + 1;
-    double *Hdev = nullptr;
-    PP_TRY(dev_alloc(&Hdev, (size_t)ld * d));
-    struct Free {
-        double *p;
-        ~Free() { dev_free(p); }
-    } free_h{Hdev};
+    PP_TRY(A->ensure_hess((size_t)ld * d));
+    double *Hdev = A->hess;
     HIP_TRY(hipMemsetAsync(Hdev, 0, sizeof(double) * ld * d, st));
     double *dd = A->h1();    // reduced dots, then g (3 d + 6 values over h1, h2, H)
     double *pend = A->z();   // first-pass coefficients of the pending column
@@ -3136,7 +3143,7 @@ pp_status pp_solve_workspace_bytes(pp_poly p, pp_matrix A, const pp_solve_opts *
     if (d_new > 0) {
         const int64_t h = (int64_t)sizeof(double) * (d_new + 1) * d_new;
         tot += h;
-        add += h;
+        if ((size_t)h > A->hess_len * sizeof(double)) add += h;
     }
     if (total) *total = tot;
     if (additional) *additional = add;
