@@ -266,13 +266,16 @@ pp_status pp_matrix_march_shape(pp_matrix A, int prec, int *shape);
  * the grid. p chains' accumulators are read and written once per launch. The
  * results equal single launches up to the order of rounding. pp_matrix_tune
  * times the likeliest shapes and keeps the fastest when it beats the others.
- *   pp_matrix_set_grid: forces a shape (steps 2..32; 0 turns it off);
+ * On a 3-D grid (7-point stencils with constant coefficients) the workgroup
+ * marches its 64 vx x waves ry region through the planes with 2 or 3 steps in
+ * flight; the tuner chooses for programs with and without an accumulator apart.
+ *   pp_matrix_set_grid: forces a shape (steps 2..32, 3-D 2..3; 0 turns it off);
  *     PP_EINVAL where it does not apply, for a shape that is not built or
  *     whose region leaves no tile, for bfloat16 vectors, or for a precision
  *     not tuned or set yet. pp_matrix_set_variant and the other fusion
  *     controls turn it off.
  *   pp_matrix_grid: shape (host int[4]) = {vx, ry, waves, steps} in use
- *     (steps 0: off), us the tuned time of one launch (0: forced). */
+ *     (steps 0: off; 3-D: by phi(A)v), us the tuned time of one launch (0: forced). */
 pp_status pp_matrix_set_grid(pp_matrix A, int prec, int vx, int ry, int waves, int steps);
 pp_status pp_matrix_grid(pp_matrix A, int prec, int *shape, double *us);
 

@@ -183,13 +183,13 @@ class Matrix:
         return v.value
 
     def set_grid(self, prec: str, vx: int, ry: int, waves: int, steps: int):
-        """Up to `steps` (2..32) chain steps per launch on a 2-D grid stencil,
-        regions of 64 vx x waves ry points (steps 0: off)."""
+        """Up to `steps` (2..32; 3-D: 2 or 3) chain steps per launch on a grid
+        stencil, regions of 64 vx x waves ry points (steps 0: off)."""
         check(lib.pp_matrix_set_grid(self.handle, PREC[prec], int(vx), int(ry), int(waves), int(steps)),
               "pp_matrix_set_grid")
 
     def grid(self, prec: str = "fp32"):
-        """((vx, ry, waves, steps), tuned us per launch) of the 2-D multi-step kernel (steps 0: off)."""
+        """((vx, ry, waves, steps), tuned us per launch) of the grid multi-step kernel (steps 0: off; 3-D: for phi)."""
         sh, us = (ctypes.c_int * 4)(), ctypes.c_double()
         check(lib.pp_matrix_grid(self.handle, PREC[prec], sh, ctypes.byref(us)), "pp_matrix_grid")
         return tuple(sh), us.value

@@ -19,6 +19,7 @@
 
 #include "../../include/ppgmres.h"
 #include "grid2.h"
+#include "grid3.h"
 #include "host_core.h"
 #include "kernels.h"
 #include "poly.h"
@@ -129,9 +130,31 @@ struct pp_matrix_s {
         }
         return m;
     }
-    void grid2_off(int prec) {
-        g2[prec] = Grid2Shape();
-        g2_us[prec] = 0.0;
+    // The same for constant-coefficient 7-point boxes, apart for programs
+    // without [0] and with an accumulator [1]: the kernels they replace differ
+    Grid2Shape g3[3][2];
+    double g3_us[3][2] = {};
+    bool has_grid3() const { return box_nd == 7 && box_pint >= 0 && ptab64; }
+    Grid3Mat grid3() const {
+        Grid3Mat m;
+        m.gx = (int)box[0];
+        m.gy = (int)box[1];
+        m.gz = (int)box[2];
+        if (has_grid3()) {
+            m.coef64 = ptab64 + (size_t)box_pint * 7;
+            m.coef32 = ptab32 + (size_t)box_pint * 7;
+        }
+        return m;
+    }
+    // the shape of a program with (without) an accumulator; steps 0: none
+    const Grid2Shape &grid(int prec, bool acc) const { return box_nd == 7 ? g3[prec][acc] : g2[prec]; }
+    void grid_off(int prec) {
+        g2[prec] = g3[prec][0] = g3[prec][1] = Grid2Shape();
+        g2_us[prec] = g3_us[prec][0] = g3_us[prec][1] = 0.0;
+    }
+    hipError_t launch_grid(int prec, const Grid2Shape &s, const Grid2Ptrs &p, hipStream_t st) const {
+        return box_nd == 7 ? launch_chain_grid3(grid3(), prec, s, p, 1, st)
+                           : launch_chain_grid2(grid2(), prec, s, p, 1, st);
     }
     // column-banded CSR copies (matrices whose entries lie far from the
     // diagonal): c = 0 two bands, c = 1 four; bperm maps entries to CSR
@@ -607,7 +630,7 @@ void grid2_shapes(const Grid2Mat &m, int prec, std::vector<Grid2Shape> &out) {
 // lowest time per step when it beats `single`, a step's time in a launch of
 // its own.
 pp_status tune_grid2(pp_matrix A, int prec, double single, hipEvent_t e0, hipEvent_t e1, hipStream_t st) {
-    A->grid2_off(prec);
+    A->grid_off(prec);
     if (A->g2_nd == 0 || prec == PP_BF16S) return PP_OK;
     const Workspace &w = A->ws[prec];
     const Grid2Mat m = A->grid2();
@@ -634,6 +657,65 @@ pp_status tune_grid2(pp_matrix A, int prec, double single, hipEvent_t e0, hipEve
             best = us / s.steps;
             A->g2[prec] = s;
             A->g2_us[prec] = us;
+        }
+    }
+    return PP_OK;
+}
+
+// The 3-D kernel's shapes worth timing: each built one with the largest
+// workgroup and its half, waves trimmed to the rows that the tiles share out evenly.
+void grid3_shapes(const Grid3Mat &m, int prec, std::vector<Grid2Shape> &out) {
+    out.clear();
+    for (int steps = 2; steps <= kGrid3MaxSteps; ++steps)
+        for (int vx = 1; vx <= 2; ++vx)
+            for (int ry = 2; ry <= 4; ry += 2)
+                for (int half = 0; half < 2; ++half) {
+                    Grid2Shape s;
+                    s.vx = vx;
+                    s.ry = ry;
+                    s.steps = steps;
+                    s.waves = grid3_max_waves(prec, vx, ry) >> half;
+                    int tx, ty;
+                    long tiles;
+                    if (!grid3_built(m, prec, s) || !grid3_fit(m, s)) continue;
+                    grid3_tiles(m, s, steps, &tx, &ty, &tiles);
+                    const int nty = (m.gy + ty - 1) / ty;
+                    const int rows = (m.gy + nty - 1) / nty + (nty > 1 ? 2 * steps : 0);
+                    s.waves = std::min(s.waves, (rows + ry - 1) / ry);
+                    if (grid3_fit(m, s)) out.push_back(s);
+                }
+}
+
+// Time the 3-D multi-step kernel and keep the shape with the lowest time per
+// step when it beats `other`, a step's time in the launches it would replace.
+pp_status tune_grid3(pp_matrix A, int prec, bool acc, double other, hipEvent_t e0, hipEvent_t e1, hipStream_t st) {
+    A->g3[prec][acc] = Grid2Shape();
+    A->g3_us[prec][acc] = 0.0;
+    if (!A->has_grid3() || prec == PP_BF16S) return PP_OK;
+    const Workspace &w = A->ws[prec];
+    const Grid3Mat m = A->grid3();
+    std::vector<Grid2Shape> shapes;
+    grid3_shapes(m, prec, shapes);
+    Grid2Step<double> u[kGrid3MaxSteps];
+    for (auto &t : u) t = Grid2Step<double>{1.0, 1.0, 0.0, 1.0, 0.0, 0};
+    double best = other;
+    for (const Grid2Shape &s : shapes) {
+        const Grid2Ptrs gp{w.P0, w.P1, acc ? w.T : nullptr, 1, nullptr, u, s.steps};
+        double us = 1e30;
+        for (int round = 0; round < 2; ++round) {
+            HIP_TRY(launch_chain_grid3(m, prec, s, gp, 1, st));
+            HIP_TRY(hipEventRecord(e0, st));
+            for (int i = 0; i < 5; ++i) HIP_TRY(launch_chain_grid3(m, prec, s, gp, 1, st));
+            HIP_TRY(hipEventRecord(e1, st));
+            HIP_TRY(hipEventSynchronize(e1));
+            float ms = 0.f;
+            HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
+            us = std::min(us, 1e3 * ms / 5);
+        }
+        if (us / s.steps < best) {
+            best = us / s.steps;
+            A->g3[prec][acc] = s;
+            A->g3_us[prec][acc] = us;
         }
     }
     return PP_OK;
@@ -757,6 +839,7 @@ pp_status tune_chain(pp_matrix A, int prec, hipStream_t st) {
         }
         A->pair_us[prec] = bp;
         A->fuse[prec] = bp < 2.0 * single_acc ? 1 : 0;
+        PP_TRY(tune_grid3(A, prec, true, std::min(0.5 * bp, single_acc), e0, e1, st));
     }
     // 2 to kMarchMax steps per launch of the marching kernel: each launch
     // length is timed over a few plane-chunk sizes; the length with the
@@ -839,7 +922,8 @@ pp_status tune_chain(pp_matrix A, int prec, hipStream_t st) {
                 A->march[prec] = g;
             }
         }
-        if (A->g2[prec].steps > 0 && A->g2_us[prec] / A->g2[prec].steps >= per_step) A->grid2_off(prec);
+        if (A->g2[prec].steps > 0 && A->g2_us[prec] / A->g2[prec].steps >= per_step) A->grid_off(prec);
+        PP_TRY(tune_grid3(A, prec, false, per_step, e0, e1, st));
     }
     // The persistent kernel is only timed on request: its grid barrier must
     // write back and invalidate the per-XCD L2 caches, which costs far more
@@ -947,7 +1031,7 @@ int march_group_len(const std::vector<Step> &prog, size_t i, int smax) {
 
 // One launch of a chain program as run_program issues it.
 struct Planned {
-    int kind;   // 0: one step, 1: the two-step pair kernel, 2: the marching kernel, 3: the 2-D multi-step kernel
+    int kind;   // 0: one step, 1: the two-step pair kernel, 2: the marching kernel, 3: the 2-D or 3-D multi-step kernel
     int i, g;   // steps i .. i+g-1
     int write;  // the buffer the launch's last result goes to
     int swap;   // after the launch the names `write` and the last step's out swap (-1: no swap)
@@ -960,10 +1044,11 @@ struct Planned {
 // dead after the group and the two names swap for the rest of the program.
 void plan_program(pp_matrix A, const std::vector<Step> &prog, int prec, std::vector<Planned> &out) {
     out.clear();
-    if (A->g2[prec].steps > 0 && !A->persist[prec] && linear_program(prog)) {
+    const int gsteps = prog.empty() ? 0 : A->grid(prec, prog[0].acc != B_NONE).steps;
+    if (gsteps > 0 && !A->persist[prec] && linear_program(prog)) {
         // each launch reads what the one before it wrote, two temporaries in turn
         int i = 0, to = B_P0;
-        for (int g : split_program(prog, A->g2[prec].steps)) {
+        for (int g : split_program(prog, gsteps)) {
             const bool last = i + g == (int)prog.size();
             out.push_back(Planned{3, i, g, last ? prog.back().out : to, -1});
             to = to == B_P0 ? B_P1 : B_P0;
@@ -1054,7 +1139,24 @@ pp_status run_program(pp_matrix A, pp_poly poly, int kind, int prec, const void 
                 if (t.acc_init) gp.load_acc = 0;
             }
             gp.acc = ptr(s.acc);
-            HIP_TRY(launch_chain_grid2(A->grid2(), prec, A->g2[prec], gp, 1, st));
+            if (A->box_nd == 7 && L.g == 1) {  // what the split leaves over
+                StepPtrs p;
+                p.in = chain;
+                p.aux = nullptr;
+                p.vfin = gp.vfin;
+                p.out = gp.out;
+                p.acc = gp.acc;
+                p.acc_init = s.acc_init;
+                p.spmv = 1;
+                p.a0 = s.a0;
+                p.a1 = s.a1;
+                p.a2 = 0.0;
+                p.b0 = s.b0;
+                p.b1 = s.b1;
+                HIP_TRY(launch_chain_step(d, prec, p, st));
+            } else {
+                HIP_TRY(A->launch_grid(prec, A->grid(prec, gp.acc != nullptr), gp, st));
+            }
             chain = gp.out;
             continue;
         }
@@ -1279,8 +1381,8 @@ void program_bytes(pp_matrix A, pp_poly poly, int kind, int prec, int64_t &bytes
         if (L.kind == 3) {
             // the coefficients (or the diagonal format's values), the input,
             // the accumulator or the final vector, the output: each once
-            const int64_t slots = A->g2_pint >= 0 ? 1 : ((int64_t)A->n + 255) / 256 * 256;
-            bytes += slots * A->g2_nd * csz + vec * (1 + (t.out != B_NONE) + (t.fin != 0));
+            const int64_t slots = A->box_nd == 7 || A->g2_pint >= 0 ? 1 : ((int64_t)A->n + 255) / 256 * 256;
+            bytes += slots * (A->box_nd == 7 ? 7 : A->g2_nd) * csz + vec * (1 + (t.out != B_NONE) + (t.fin != 0));
             if (s.acc != B_NONE) bytes += vec * (s.acc_init ? 1 : 2);
             launches += 1;
             continue;
@@ -2205,11 +2307,12 @@ pp_status refresh_values(pp_matrix A, const double *val, hipStream_t st) {
             // a tuned multi-step shape may not be built for per-row values:
             // the model's first choice takes its place
             for (int p = 0; p < 3; ++p) {
+                if (A->box_nd == 7 && !A->has_grid3()) A->grid_off(p);
                 if (A->g2[p].steps == 0 || (grid2_built(A->grid2(), p, A->g2[p].vx, A->g2[p].ry) && A->g2_pint >= 0)) continue;
                 std::vector<Grid2Shape> shapes;
                 grid2_shapes(A->grid2(), p, shapes);
                 if (shapes.empty())
-                    A->grid2_off(p);
+                    A->grid_off(p);
                 else
                     A->g2[p] = shapes[0];
             }
@@ -2557,7 +2660,7 @@ pp_status pp_matrix_set_variant(pp_matrix A, int prec, int variant, int remap) {
     A->march_all[prec] = 0;
     A->march_tile[prec] = 0;
     A->pair_tile[prec] = 0;
-    A->grid2_off(prec);
+    A->grid_off(prec);
     return PP_OK;
 }
 
@@ -2576,7 +2679,7 @@ pp_status pp_matrix_set_pair_steps(pp_matrix A, int prec, int mode) {
         return PP_EINVAL;
     }
     A->fuse[prec] = mode;
-    A->grid2_off(prec);
+    A->grid_off(prec);
     return PP_OK;
 }
 
@@ -2595,7 +2698,7 @@ pp_status pp_matrix_set_march(pp_matrix A, int prec, int steps, int cz, int dept
         set_error("pp_matrix_set_march: tune or set a single-launch variant for this precision first");
         return PP_EINVAL;
     }
-    A->grid2_off(prec);
+    A->grid_off(prec);
     A->march[prec] = steps;
     A->march_all[prec] = steps >= 2;
     A->march_tile[prec] = 0;
@@ -2621,7 +2724,7 @@ pp_status pp_matrix_set_march_shape(pp_matrix A, int prec, int shape) {
                   "whose grid lines hold 64, 128 or 256 points, and FP64 or FP32 vectors");
         return PP_EINVAL;
     }
-    A->grid2_off(prec);
+    A->grid_off(prec);
     A->march_tile[prec] = shape;
     A->pair_tile[prec] = shape;
     if (shape == 1) {
@@ -2648,14 +2751,21 @@ pp_status pp_matrix_set_grid(pp_matrix A, int prec, int vx, int ry, int waves, i
     s.steps = steps;
     int tx, ty;
     long tiles;
-    if (steps > 0 && (A->g2_nd == 0 || !grid2_built(A->grid2(), prec, vx, ry) ||
-                      !grid2_tiles(A->grid2(), s, steps, &tx, &ty, &tiles))) {
-        set_error("pp_matrix_set_grid: needs a 5- or 13-point stencil on a 2-D grid (13 points: constant "
-                  "coefficients), FP64 or FP32 vectors, and a built shape whose region leaves a tile");
+    const bool ok = A->box_nd == 7 ? A->has_grid3() && grid3_built(A->grid3(), prec, s) && grid3_fit(A->grid3(), s)
+                                   : A->g2_nd != 0 && grid2_built(A->grid2(), prec, vx, ry) &&
+                                         grid2_tiles(A->grid2(), s, steps, &tx, &ty, &tiles);
+    if (steps > 0 && !ok) {
+        set_error("pp_matrix_set_grid: needs a 5- or 13-point stencil on a 2-D grid or a 7-point one on a 3-D grid "
+                  "(7 and 13 points: constant coefficients), FP64 or FP32 vectors, and a built shape whose region leaves a tile");
         return PP_EINVAL;
     }
-    A->grid2_off(prec);
-    if (steps > 0) A->g2[prec] = s;
+    A->grid_off(prec);
+    if (steps > 0) {
+        if (A->box_nd == 7)
+            A->g3[prec][0] = A->g3[prec][1] = s;
+        else
+            A->g2[prec] = s;
+    }
     return PP_OK;
 }
 
@@ -2664,12 +2774,12 @@ pp_status pp_matrix_grid(pp_matrix A, int prec, int *shape, double *us) {
         set_error("pp_matrix_grid: bad argument");
         return PP_EINVAL;
     }
-    const Grid2Shape &s = A->g2[prec];
+    const Grid2Shape &s = A->grid(prec, false);
     shape[0] = s.vx;
     shape[1] = s.ry;
     shape[2] = s.waves;
     shape[3] = s.steps;
-    if (us) *us = A->g2_us[prec];
+    if (us) *us = A->box_nd == 7 ? A->g3_us[prec][0] : A->g2_us[prec];
     return PP_OK;
 }
 
@@ -3296,7 +3406,8 @@ pp_status pp_solve(pp_poly p, pp_matrix A, const double *b, double *x, const pp_
         // by more than that ratio.
         bool ahead = false;
         double r_last = beta, rate = 1.0;
-        const double t_step = A->g2[prec].steps > 0 && A->g2_us[prec] > 0.0 ? A->g2_us[prec] / A->g2[prec].steps
+        const double g_us = A->box_nd == 7 ? A->g3_us[prec][0] : A->g2_us[prec];
+        const double t_step = g_us > 0.0             ? g_us / A->grid(prec, false).steps
                               : A->tuned_us[prec] > 0.0                      ? A->tuned_us[prec]
                                                                              : kLaunchGuessUs;
         const double t_phi = (double)chain_launches(p, PP_APPLY_PHI) * t_step;

@@ -45,6 +45,7 @@ struct Grid2Mat {
 struct Grid2Shape {
     int vx = 0, ry = 0, waves = 0;
     int steps = 0;  // steps per launch
+    int tz = 0;     // planes per chunk (3-D grids)
 };
 
 // The (vx, ry) pairs that are built for this matrix and precision (0: FP64, 1: FP32).

@@ -50,6 +50,33 @@ __device__ __forceinline__ Grid2Step<AT> lane_step(const Grid2Step<AT> &s, int k
 __device__ __forceinline__ void loaded(float &v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void loaded(double &v) { asm volatile("" : "+v"(v)); }
 
+// VX adjacent points of a grid line (p, gx points) from column x: line_load
+// reads them, line_pick drops what lies outside the line. Two columns are
+// one access on an element-aligned address, moved inside the line and
+// picked apart.
+template <typename AT, int VX>
+__device__ __forceinline__ void line_load(const AT *p, int x, int gx, AT *o) {
+    if constexpr (VX == 1) {
+        o[0] = p[min(max(x, 0), gx - 1)];
+    } else {
+        typedef AT Pair __attribute__((ext_vector_type(2), aligned(sizeof(AT))));
+        const Pair t = *reinterpret_cast<const Pair *>(p + min(max(x, 0), gx - 2));
+        o[0] = t[0];
+        o[1] = t[1];
+    }
+}
+template <typename AT, int VX>
+__device__ __forceinline__ void line_pick(int x, int gx, bool in, AT *o) {
+    if constexpr (VX == 1) {
+        o[0] = in && x >= 0 && x < gx ? o[0] : AT(0);
+    } else {
+        const int xb = min(max(x, 0), gx - 2);
+        const AT t0 = o[0], t1 = o[1];
+        o[0] = in && x >= 0 && x < gx ? (x == xb ? t0 : t1) : AT(0);
+        o[1] = in && x + 1 >= 0 && x + 1 < gx ? (x + 1 == xb ? t0 : t1) : AT(0);
+    }
+}
+
 // A wave owns RY consecutive grid rows of 64 VX columns, a lane VX adjacent
 // columns of them with NC interleaved values per point (NV = VX NC values a
 // row). The column neighbours are lane moves, the row neighbours the lane's
