@@ -1487,11 +1487,10 @@ pp_status spmv_axpby(pp_matrix A, int prec, const void *in, double a0, const voi
 }
 
 // Orthogonalise w = V[:, j+1] against V[:, 0..j] by classical Gram-Schmidt
-// applied twice, normalise it, and leave the Hessenberg column
-// (j+2 values) in A->hpin (host) after a stream synchronisation.
-pp_status cgs2_step(pp_matrix A, int prec, const Workspace &ws, int j, hipStream_t st, double *Hcol = nullptr,
-                    bool to_host = true) {
-    if (!Hcol) Hcol = A->H();
+// applied twice and normalise it; the Hessenberg column (j+2 values) is in
+// A->hpin (host) once the stream has run it.
+pp_status cgs2_step(pp_matrix A, int prec, const Workspace &ws, int j, hipStream_t st) {
+    double *Hcol = A->H();
     const int n = A->n;
     const int ncols = j + 1;
     void *w = vcol(ws, prec, j + 1);
@@ -1504,8 +1503,7 @@ pp_status cgs2_step(pp_matrix A, int prec, const Workspace &ws, int j, hipStream
     if (ncols <= update_dots_max_cols(prec)) {
         HIP_TRY(launch_update_dots(prec, n, ws.V, ws.ldv, ncols, A->h1(), w, A->partial, A->ldp, st));
         HIP_TRY(launch_reduce(A->nblk_ud, A->partial, A->ldp, ncols + 1, A->h2(), nullptr, 0, st));
-        HIP_TRY(launch_finish_col(ncols, A->h2(), Hcol, A->inv(), st));
-        HIP_TRY(launch_update_scale(prec, n, ws.V, ws.ldv, ncols, A->h2(), w, A->inv(), st));
+        HIP_TRY(launch_update_scale(prec, n, ws.V, ws.ldv, ncols, A->h2(), w, Hcol, A->hpin, st));
     } else {
         HIP_TRY(launch_update(prec, n, ws.V, ws.ldv, ncols, A->h1(), w, nullptr, st));
         HIP_TRY(launch_dots(prec, n, ws.V, ws.ldv, ncols, w, A->partial, A->ldp, st));
@@ -1514,12 +1512,10 @@ pp_status cgs2_step(pp_matrix A, int prec, const Workspace &ws, int j, hipStream
         HIP_TRY(launch_update(prec, n, ws.V, ws.ldv, ncols, A->h2(), w, A->npart, st));
         HIP_TRY(launch_reduce_norm(A->nblk_upd, A->npart, Hcol + ncols, A->inv(), st));
         HIP_TRY(launch_scale_cast(prec, prec, n, w, A->inv(), 0.0, w, st));
+        HIP_TRY(hipMemcpyAsync(A->hpin, Hcol, sizeof(double) * (ncols + 1), hipMemcpyDeviceToHost, st));
     }
-    if (!to_host) return PP_OK;
-    HIP_TRY(hipMemcpyAsync(A->hpin, Hcol, sizeof(double) * (ncols + 1), hipMemcpyDeviceToHost, st));
     HIP_TRY(copy_barrier_flag(A, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    return check_barrier_flag(A);
+    return PP_OK;
 }
 
 // ||x|| of a device vector (synchronises); x is not modified.
@@ -3414,9 +3410,7 @@ pp_status pp_solve(pp_poly p, pp_matrix A, const double *b, double *x, const pp_
         const double margin = std::max(2.0, t_phi / kLookaheadGapUs);
         for (int j = 0; j < m; ++j) {
             if (!ahead) PP_TRY(run_program(A, p, PP_APPLY_PHI, prec, vcol(ws, prec, j), vcol(ws, prec, j + 1), st));
-            PP_TRY(cgs2_step(A, prec, ws, j, st, nullptr, false));
-            HIP_TRY(hipMemcpyAsync(A->hpin, A->H(), sizeof(double) * (j + 2), hipMemcpyDeviceToHost, st));
-            HIP_TRY(copy_barrier_flag(A, st));
+            PP_TRY(cgs2_step(A, prec, ws, j, st));
             HIP_TRY(hipEventRecord(col_ready.e, st));
             // V[:, j+1] is final once the step's kernels ran: queue the next
             // step's product unless this step is expected to end the cycle

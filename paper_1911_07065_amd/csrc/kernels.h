@@ -295,11 +295,10 @@ int update_dots_max_cols(int prec);
 hipError_t launch_update_dots(int prec, int n, const void *V, long ldv, int ncols, const double *h, void *w,
                               double *partial, int ldp, hipStream_t st);
 // (partial column ncols of launch_update_dots holds the block's ||w_new||^2)
-// H[k] += h2[k]; H[ncols] = sqrt(h2[ncols] - ||h2||^2); inv[0] = 1/H[ncols] (0 if 0).
-hipError_t launch_finish_col(int ncols, const double *h2, double *H, double *inv, hipStream_t st);
-// w = (w - V h) * inv[0]
+// w = (w - V h) / nrm, nrm = sqrt(h[ncols] - ||h[0:ncols]||^2) (zero: w = 0);
+// H[0:ncols] += h, H[ncols] = nrm, and both to host (device-visible host memory).
 hipError_t launch_update_scale(int prec, int n, const void *V, long ldv, int ncols, const double *h, void *w,
-                               const double *inv, hipStream_t st);
+                               double *H, double *host, hipStream_t st);
 // norm = sqrt(sum_b partial[b]); writes H[0] = norm, inv[0] = 1/norm (0 if norm == 0).
 hipError_t launch_reduce_norm(int nblk, const double *partial, double *H, double *inv, hipStream_t st);
 // out[i] = (T_out)(in[i] * s) with s = scale[0] (device) or, if scale is null,
