@@ -94,6 +94,23 @@ __device__ __forceinline__ T block_sum256(T v, T *sm /* [4] */) {
     return r;
 }
 
+// The value of the lane to the left (lane - 1; zero in lane 0) or to the
+// right (lane + 1; zero in lane 63): a VALU move across the whole wave.
+__device__ __forceinline__ float lane_left(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float lane_right(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double lane_left(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xF, 0xF, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double lane_right(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xF, 0xF, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xF, 0xF, true));
+}
+
 __device__ __forceinline__ int remap_tile(int b, int ntiles, int remap) {
     if (!remap) return b;
     constexpr int nx = 8;  // XCDs; workgroups are dispatched round-robin over them

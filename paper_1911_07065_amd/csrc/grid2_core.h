@@ -11,23 +11,6 @@
 namespace ppg {
 namespace {
 
-// The value of the lane to the left (lane - 1; zero in lane 0) or to the
-// right (lane + 1; zero in lane 63): a VALU move across the whole wave.
-__device__ __forceinline__ float lane_left(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xF, 0xF, true));
-}
-__device__ __forceinline__ float lane_right(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xF, 0xF, true));
-}
-__device__ __forceinline__ double lane_left(double v) {
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xF, 0xF, true),
-                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xF, 0xF, true));
-}
-__device__ __forceinline__ double lane_right(double v) {
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xF, 0xF, true),
-                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xF, 0xF, true));
-}
-
 __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 

@@ -1770,9 +1770,11 @@ __global__ __launch_bounds__(256) void k_chain_march(MarchArgs<XT> a, const uint
 //     out = vfin ? vfin - w2 : w2                          (if out)
 // so a p chain's pair reads and writes its accumulator once, and w1 never
 // leaves LDS. NTH threads; a lane owns 4 consecutive points of a line (GX / 4
-// lanes per line): the line itself, the lines above and below in y and z are
-// one 4-wide LDS access each, the two neighbours along the line single
-// accesses. Products are summed in ascending diagonal order with the interior
+// lanes per line) and takes two lines adjacent in z at a time: eight 4-wide LDS
+// accesses, the neighbours along the lines by lane moves. One line at a time
+// with single LDS accesses for those took 6.9 us a launch on 128^3 in FP32,
+// this 6.65 (FP64 64^3: 5.5 and 5.0); what is left is the launch and the
+// trips to memory, which nothing overlaps with one workgroup per CU. Products are summed in ascending diagonal order with the interior
 // row's coefficients, as the other kernels do. There is no x halo and no
 // per-point index arithmetic; the price is the two-line halo in y and z.
 template <typename XT>
@@ -1790,12 +1792,15 @@ template <typename VT, typename XT, int TY, int TZ, int GX, int NTH>
 __global__ __launch_bounds__(NTH) void k_chain_boxt(BoxtArgs<XT> a, const VT *__restrict__ ptab, int remap) {
     using AT = typename Arith<XT>::T;
     typedef AT AV4 __attribute__((ext_vector_type(4)));
-    static_assert(GX % 4 == 0 && NTH % (GX / 4) == 0, "whole lines of 4-point lanes in a workgroup");
+    static_assert(GX % 4 == 0 && NTH % (GX / 4) == 0 && TZ % 2 == 0 && GX <= 256, "whole lines of 4-point lanes in a wave");
     constexpr int LPL = GX / 4, LPP = NTH / LPL;  // lanes per line, lines per pass
     constexpr int RY0 = TY + 4, NL0 = RY0 * (TZ + 4);
     constexpr int RY1 = TY + 2, NL1 = RY1 * (TZ + 2);
-    constexpr int NT = TY * TZ;
-    constexpr int C0 = (NL0 + LPP - 1) / LPP, C1 = (NL1 + LPP - 1) / LPP, CT = (NT + LPP - 1) / LPP;
+    // lines adjacent in z that a lane takes at once: two, unless that leaves
+    // half of the lanes without a line of the tile
+    constexpr int NZ1 = 2, NZ2 = TY * TZ / 2 >= LPP ? 2 : 1;
+    constexpr int NP1 = NL1 / NZ1, NP2 = TY * TZ / NZ2;
+    constexpr int C0 = (NL0 + LPP - 1) / LPP, C1 = (NP1 + LPP - 1) / LPP, C2 = (NP2 + LPP - 1) / LPP;
     __shared__ AV4 lev0[NL0 * LPL];
     __shared__ AV4 lev1[NL1 * LPL];
     const int tid = threadIdx.x, li = tid / LPL, lx = tid % LPL, x = 4 * lx;
@@ -1818,16 +1823,19 @@ __global__ __launch_bounds__(NTH) void k_chain_boxt(BoxtArgs<XT> a, const VT *__
         ld4(a.in, zc * P + (long)yc * GX + x, pre[k]);
     }
     const bool load_acc = a.acc && !a.init;
-    AT vf[CT][4], pa[CT][4];
+    AT vf[C2][NZ2][4], pa[C2][NZ2][4];
 #pragma unroll
-    for (int k = 0; k < CT; ++k) {
-        const int L = min(li + k * LPP, NT - 1);
-        const int y = min(y0 + L % TY, gy - 1), z = min(z0 + L / TY, gz - 1);
-        const long r = z * P + (long)y * GX + x;
+    for (int k = 0; k < C2; ++k) {
+        const int q = min(li + k * LPP, NP2 - 1);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) vf[k][i] = pa[k][i] = AT(0);
-        if (a.vfin) ld4(a.vfin, r, vf[k]);
-        if (load_acc) ld4(a.acc, r, pa[k]);
+        for (int h = 0; h < NZ2; ++h) {
+            const int y = min(y0 + q % TY, gy - 1), z = min(z0 + q / TY * NZ2 + h, gz - 1);
+            const long r = z * P + (long)y * GX + x;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) vf[k][h][i] = pa[k][h][i] = AT(0);
+            if (a.vfin) ld4(a.vfin, r, vf[k][h]);
+            if (load_acc) ld4(a.acc, r, pa[k][h]);
+        }
     }
 #pragma unroll
     for (int k = 0; k < C0; ++k) {
@@ -1837,67 +1845,78 @@ __global__ __launch_bounds__(NTH) void k_chain_boxt(BoxtArgs<XT> a, const VT *__
         if (L < NL0) lev0[L * LPL + lx] = in ? AV4{pre[k][0], pre[k][1], pre[k][2], pre[k][3]} : AV4{0, 0, 0, 0};
     }
     __syncthreads();
-    // one step on a line of an LDS region with RY lines per z slice
-    auto step = [&](const AV4 *src, int line, int RY, AT a0, AT a1) -> AV4 {
-        const AV4 cc = src[line * LPL + lx];
-        const AV4 ym = src[(line - 1) * LPL + lx], yp = src[(line + 1) * LPL + lx];
-        const AV4 zm = src[(line - RY) * LPL + lx], zp = src[(line + RY) * LPL + lx];
-        const AT *sl = reinterpret_cast<const AT *>(src + line * LPL);
-        const AT xl = x > 0 ? sl[max(x - 1, 0)] : AT(0);
-        const AT xr = x + 4 < GX ? sl[min(x + 4, GX - 1)] : AT(0);
-        const AT xv[6] = {xl, cc[0], cc[1], cc[2], cc[3], xr};
-        AV4 w;
+    // one step on W's lines of an LDS region with RY lines per z slice, the
+    // first of them `line`, each the next in z
+    auto step = [&](const AV4 *src, int line, int RY, AT a0, AT a1, auto &w) {
+        constexpr int NZ = (int)(sizeof(w) / sizeof(AV4));
+        AV4 col[NZ + 2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            AT s = AT(0);
-            s += c[0] * zm[i];
-            s += c[1] * ym[i];
-            s += c[2] * xv[i];
-            s += c[3] * xv[i + 1];
-            s += c[4] * xv[i + 2];
-            s += c[5] * yp[i];
-            s += c[6] * zp[i];
-            w[i] = a0 * s + a1 * xv[i + 1];
+        for (int h = 0; h < NZ + 2; ++h) col[h] = src[(line + (h - 1) * RY) * LPL + lx];
+#pragma unroll
+        for (int h = 0; h < NZ; ++h) {
+            const AV4 ym = src[(line + h * RY - 1) * LPL + lx], yp = src[(line + h * RY + 1) * LPL + lx];
+            const AV4 cc = col[h + 1];
+            // the neighbours along the line are the next lanes' (a line lies in
+            // one wave); the line's ends drop what the next line's lanes hold
+            const AT xl = lane_left((AT)cc[3]), xr = lane_right((AT)cc[0]);
+            const AT xv[6] = {x > 0 ? xl : AT(0), cc[0], cc[1], cc[2], cc[3], x + 4 < GX ? xr : AT(0)};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                AT s = AT(0);
+                s += c[0] * col[h][i];
+                s += c[1] * ym[i];
+                s += c[2] * xv[i];
+                s += c[3] * xv[i + 1];
+                s += c[4] * xv[i + 2];
+                s += c[5] * yp[i];
+                s += c[6] * col[h + 2][i];
+                w[h][i] = a0 * s + a1 * xv[i + 1];
+            }
         }
-        return w;
     };
     // the first step on the tile's lines and one line around them
 #pragma unroll
     for (int k = 0; k < C1; ++k) {
-        const int L = li + k * LPP;
-        if (L < NL1) {
-            const int ly = L % RY1, lz = L / RY1;
+        const int q = li + k * LPP;
+        if (q < NP1) {
+            const int ly = q % RY1, lz = q / RY1 * NZ1;
             const int y = y0 - 1 + ly, z = z0 - 1 + lz;
-            AV4 w = AV4{0, 0, 0, 0};
-            if (y >= 0 && y < gy && z >= 0 && z < gz) w = step(lev0, (ly + 1) + RY0 * (lz + 1), RY0, a.a01, a.a11);
-            lev1[L * LPL + lx] = w;
+            AV4 w[NZ1];
+            step(lev0, (ly + 1) + RY0 * (lz + 1), RY0, a.a01, a.a11, w);
+#pragma unroll
+            for (int h = 0; h < NZ1; ++h) {
+                const bool in = y >= 0 && y < gy && z + h >= 0 && z + h < gz;
+                lev1[(ly + RY1 * (lz + h)) * LPL + lx] = in ? w[h] : AV4{0, 0, 0, 0};
+            }
         }
     }
     __syncthreads();
     // the second step on the tile's lines, its accumulator update, stored
 #pragma unroll
-    for (int k = 0; k < CT; ++k) {
-        const int L = li + k * LPP;
-        if (L < NT) {
-            const int ly = L % TY, lz = L / TY;
-            const int y = y0 + ly, z = z0 + lz;
-            if (y < gy && z < gz) {
-                const int q1 = (ly + 1) + RY1 * (lz + 1);
-                AV4 w2 = step(lev1, q1, RY1, a.a02, a.a12);
-                const AV4 w1 = lev1[q1 * LPL + lx];
-                const AV4 xin = lev0[((ly + 2) + RY0 * (lz + 2)) * LPL + lx];
+    for (int k = 0; k < C2; ++k) {
+        const int q = li + k * LPP;
+        if (q < NP2) {
+            const int ly = q % TY, lz = q / TY * NZ2, y = y0 + ly;
+            AV4 w[NZ2];
+            step(lev1, (ly + 1) + RY1 * (lz + 1), RY1, a.a02, a.a12, w);
+#pragma unroll
+            for (int h = 0; h < NZ2; ++h) {
+                const int z = z0 + lz + h;
+                if (y >= gy || z >= gz) continue;
+                const AV4 w1 = lev1[((ly + 1) + RY1 * (lz + h + 1)) * LPL + lx];
+                const AV4 xin = lev0[((ly + 2) + RY0 * (lz + h + 2)) * LPL + lx];
                 const long r = z * P + (long)y * GX + x;
                 if (a.aux2) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) w2[i] += a.a22 * xin[i];
+                    for (int i = 0; i < 4; ++i) w[h][i] += a.a22 * xin[i];
                 }
                 if (a.acc) {
                     AT o[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        AT cacc = pa[k][i];
+                        AT cacc = pa[k][h][i];
                         if (a.acc1) cacc = cacc + a.b01 * xin[i] + a.b11 * w1[i];
-                        if (a.acc2) cacc = cacc + a.b02 * w1[i] + a.b12 * w2[i];
+                        if (a.acc2) cacc = cacc + a.b02 * w1[i] + a.b12 * w[h][i];
                         o[i] = cacc;
                     }
                     st4(a.acc, r, o);
@@ -1905,7 +1924,7 @@ __global__ __launch_bounds__(NTH) void k_chain_boxt(BoxtArgs<XT> a, const VT *__
                 if (a.out) {
                     AT o[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) o[i] = a.vfin ? vf[k][i] - w2[i] : w2[i];
+                    for (int i = 0; i < 4; ++i) o[i] = a.vfin ? vf[k][h][i] - w[h][i] : w[h][i];
                     st4(a.out, r, o);
                 }
             }
