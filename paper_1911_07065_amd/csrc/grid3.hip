@@ -95,6 +95,19 @@ struct March3 {
             }
         }
     }
+    // Step l, read from the kernel's arguments where it is used: with an
+    // accumulator in FP64, three steps kept in scalar registers are spilled to
+    // lanes and read back value by value (201 x 150 x 97 p 8.6 us a step, 8.5
+    // so; 50^3 2.75 and 2.64). Elsewhere they fit and the reads only cost.
+    static constexpr bool kReread = SIDE == ACC && sizeof(AT) == 8;
+    static __device__ __forceinline__ Grid2Step<AT> step_args(int l) {
+        typedef __attribute__((address_space(4))) const char *Args;
+        Args q = (Args)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(G3Args<AT>, steps) + l * sizeof(Grid2Step<AT>);
+        asm volatile("" : "+s"(q));
+        typedef __attribute__((address_space(4))) const Grid2Step<AT> *Steps;
+        const Steps p = (Steps)q;
+        return Grid2Step<AT>{p->a0, p->a1, p->a2, p->b0, p->b1, p->flags};
+    }
     // edge rows of level l's plane in buffer b
     __device__ __forceinline__ AT *edge(AT *lds, int b, int l, int w, int bottom) const {
         return lds + ((((size_t)(b * S + l) * waves + w) * 2 + bottom) * VX) * 64 + lane;
@@ -152,7 +165,7 @@ struct March3 {
             if (wave + 1 == waves)
 #pragma unroll
                 for (int v = 0; v < VX; ++v) dn[v] = AT(0);
-            const Grid2Step<AT> &s = a.steps[LV - 1];
+            const Grid2Step<AT> s = kReread ? step_args(LV - 1) : a.steps[LV - 1];
             Plane &ac = C[SIDE != NONE ? c : 0];
             const Plane *B = L[LV - 1];
             const Plane &aux = L[LV >= 2 ? LV - 2 : 0][c];
