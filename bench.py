@@ -98,11 +98,26 @@ def chain_kernel_name(variant):
     if v == "box/tile2":
         return ("k_chain_boxt<float,float,16,4,128,1024> (two chain steps per launch on tiles of 16 x 4 whole "
                 "grid lines, 1024 threads, the input and the first step staged in LDS)")
+    if "/grid" in v:
+        return (f"k_grid2 / k_grid3 ({v}: up to {v.split('/grid')[1]} chain steps per launch on regions of the grid "
+                "held in registers)")
+    if v == "ldsband":
+        return ("k_lb_product + k_chain_lb_finish (ldsband: column bands of the input held in LDS, one partial sum "
+                "per band and row, then the fused chain update)")
     if v.startswith("csort"):
         wide = "true" if v == "csort2" else "false"
         return (f"k_chain_cs_tiles<float,float,{wide}> + k_chain_cs_finish ({v}: (8192-row block, column band) "
                 f"tiles whose entries are sorted by column, {v[-1]} partial row sums, then the fused chain update)")
     return f"chain step, variant {v}"
+
+
+def fused_steps(M, prec):
+    """What the tuned chain of the precision adds to its single-step variant's name."""
+    steps = M.grid(prec)[0][3]
+    if steps:
+        return f"/grid{steps}"
+    g = M.march(prec)[0]
+    return "/tile2" if g == 2 and M.march_shape(prec) == 1 else (f"/march{g}" if g >= 2 else "")
 
 
 def recorded_traffic(prec, variant, remap):
@@ -232,10 +247,8 @@ def scale_leg(pp, torch, np, N=256, nroots=16, reps=10):
     for prec, dt, sx in (("fp32", torch.float32, 4), ("fp64", torch.float64, 8)):
         M.tune(prec)
         r = chain_rate(pp, torch, np, M, poly, prec, dt, reps)
-        g = M.march(prec)[0]
-        fused = "/tile2" if g == 2 and M.march_shape(prec) == 1 else (f"/march{g}" if g >= 2 else "")
         step_us = r["ms"] * 1e3 / nroots
-        out[prec] = {"variant": r["variant"] + fused, "step_us": round(step_us, 3),
+        out[prec] = {"variant": r["variant"] + fused_steps(M, prec), "step_us": round(step_us, 3),
                      "launch_us": round(r["launch_us"], 3), "launches": r["launches"],
                      "bytes_per_launch": int(r["bytes_per_launch"]), "GBps": round(r["GBps"], 1),
                      "frac": round(r["frac"], 4),
@@ -324,7 +337,8 @@ def adjoint_leg(pp, torch, np):
         fused, _, us_pair = H.pair_steps("fp64")
         g, cz, us_m = H.march("fp64")
         return {"variant": H.variant("fp64")[0], "two_steps_per_launch": fused, "two_step_launch_us": round(us_pair, 3),
-                "march_steps_per_launch": g, "march_launch_us": round(us_m, 3)}
+                "march_steps_per_launch": g, "march_launch_us": round(us_m, 3),
+                "grid_steps_per_launch": H.grid("fp64")[0][3], "grid_launch_us": round(H.grid("fp64")[1], 3)}
 
     return {"workload": f"2-D convection-diffusion {N}^2 (n={n}, nnz={A0.nnz}), theta=20 leaf, "
                         "PP(50)-GMRES(50) to 1e-12 FP64, forward + adjoint",
@@ -769,8 +783,7 @@ def main():
 
     k32 = phi["fp32"]
     for prec in ("fp32", "fp64"):
-        if M.march(prec)[0] == 2 and M.march_shape(prec) == 1:
-            phi[prec]["variant"] += "/tile2"  # two steps per launch on whole grid lines
+        phi[prec]["variant"] += fused_steps(M, prec)
     tr = recorded_traffic("fp32", k32["variant"], k32["remap"])
     log("recorded traffic", tr)
     roofline = {

@@ -663,27 +663,30 @@ pp_status tune_grid2(pp_matrix A, int prec, double single, hipEvent_t e0, hipEve
 }
 
 // The 3-D kernel's shapes worth timing: each built one with the largest
-// workgroup and its half, waves trimmed to the rows that the tiles share out evenly.
+// workgroup and its half, waves trimmed to the rows that the tiles share out
+// evenly, and three steps (two were 1 % faster on one box of fourteen, 128 x
+// 100 x 110 phi in FP64, and 4 to 20 % slower on the others).
 void grid3_shapes(const Grid3Mat &m, int prec, std::vector<Grid2Shape> &out) {
     out.clear();
-    for (int steps = 2; steps <= kGrid3MaxSteps; ++steps)
-        for (int vx = 1; vx <= 2; ++vx)
-            for (int ry = 2; ry <= 4; ry += 2)
-                for (int half = 0; half < 2; ++half) {
-                    Grid2Shape s;
-                    s.vx = vx;
-                    s.ry = ry;
-                    s.steps = steps;
-                    s.waves = grid3_max_waves(prec, vx, ry) >> half;
-                    int tx, ty;
-                    long tiles;
-                    if (!grid3_built(m, prec, s) || !grid3_fit(m, s)) continue;
-                    grid3_tiles(m, s, steps, &tx, &ty, &tiles);
-                    const int nty = (m.gy + ty - 1) / ty;
-                    const int rows = (m.gy + nty - 1) / nty + (nty > 1 ? 2 * steps : 0);
-                    s.waves = std::min(s.waves, (rows + ry - 1) / ry);
-                    if (grid3_fit(m, s)) out.push_back(s);
-                }
+    const int steps = kGrid3MaxSteps;
+    for (int vx = 1; vx <= 2; ++vx)
+        for (int ry = 2; ry <= 4; ry += 2)
+            for (int half = 0; half < 2; ++half) {
+                Grid2Shape s;
+                s.vx = vx;
+                s.ry = ry;
+                s.steps = steps;
+                s.waves = grid3_max_waves(prec, vx, ry) >> half;
+                int tx, ty;
+                long tiles;
+                if (!grid3_built(m, prec, s) || !grid3_fit(m, s)) continue;
+                grid3_tiles(m, s, steps, &tx, &ty, &tiles);
+                const int nty = (m.gy + ty - 1) / ty;
+                const int rows = (m.gy + nty - 1) / nty + (nty > 1 ? 2 * steps : 0);
+                s.waves = std::min(s.waves, (rows + ry - 1) / ry);
+                const bool again = !out.empty() && out.back().vx == vx && out.back().ry == ry && out.back().waves == s.waves;
+                if (!again && grid3_fit(m, s)) out.push_back(s);
+            }
 }
 
 // Time the 3-D multi-step kernel and keep the shape with the lowest time per
@@ -702,7 +705,8 @@ pp_status tune_grid3(pp_matrix A, int prec, bool acc, double other, hipEvent_t e
     for (const Grid2Shape &s : shapes) {
         const Grid2Ptrs gp{w.P0, w.P1, acc ? w.T : nullptr, 1, nullptr, u, s.steps};
         double us = 1e30;
-        for (int round = 0; round < 2; ++round) {
+        // a second round only for what the first leaves in reach
+        for (int round = 0; round < 2 && (round == 0 || us / s.steps < 1.1 * best); ++round) {
             HIP_TRY(launch_chain_grid3(m, prec, s, gp, 1, st));
             HIP_TRY(hipEventRecord(e0, st));
             for (int i = 0; i < 5; ++i) HIP_TRY(launch_chain_grid3(m, prec, s, gp, 1, st));

@@ -79,7 +79,7 @@ double house(const double *u, int len, double *v) {
 // (I - beta v v^T) applied to rows r0 .. r0 + LEN - 1, columns c0 .. c1. LEN is
 // a constant and the column a pointer: with loops over a variable length the
 // two reflections took 3/4 of a setup's host time (517 us for 40 Ritz values
-// in all, 131 us now); the operations and their order are unchanged.
+// in all, 196 us now); the operations and their order are unchanged.
 template <int LEN>
 void reflect_rows(Mat &H, int r0, const double *v, double beta, int c0, int c1) {
     const int n = H.n;

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256) void k_lb_values(long m, const int32_t *eperm,
 // What bounds it: a stream of 6 bytes an entry and the band's copy to LDS. A
 // gather from L2 instead is one request an entry at 195 G/s: 250,007 rows x
 // 17 entries take 20.5 us a step in BF16 that way, 11.6 us here with the
-// launch that adds the bands up (FP32 21.4 and 15.1 us, 130,000 rows 11.4 and
+// launch that adds the bands up (FP32 21.4 and 15.5 us, 130,000 rows 11.4 and
 // 8.7 us, 500,000 rows in BF16 27.5 and 22.7 us).
 // NP: pairs of a slice loaded before it is used.
 template <typename VT, typename XT, int NP>
