@@ -226,13 +226,13 @@ struct March3 {
 };
 
 // What bounds it: the issue of the region's operations (14 a point and step
-// in FP64, 7 of them FP64), 1.6 to 2.6 times the grid's points with the halos of
-// tiles and chunks; the vectors pass through memory once per launch instead of
-// once per step. Measured per step, against the best of the other chain
-// kernels: FP64 201 x 150 x 97 phi 6.8 us (14.7), p 8.7 us (18.3), 256 x 256
-// x 200 18.2 (33.8) and 36.9 (70.1), 64^3 phi 2.5 (2.7), 30^3 2.1 (3.0); FP32
-// 201 x 150 x 97 5.2 (8.1) and 6.5 (11.0), 64^3 2.1 (2.7). Whole-line tiles stay the
-// better on 128^3 in FP32: 3.5 us against 4.4.
+// in FP64, 7 of them FP64), 1.6 to 2.6 times the grid's points with the halos
+// of tiles and chunks; the vectors pass through memory once per launch
+// instead of once per step. Measured per step, against the best of the other
+// chain kernels: FP64 201 x 150 x 97 phi 6.8 us (14.7), p 8.5 us (18.3), 256 x
+// 256 x 200 18.2 (33.8) and 36.9 (70.1), 64^3 phi 2.5 (2.7), 30^3 2.1 (3.0);
+// FP32 201 x 150 x 97 5.2 (8.1) and 6.5 (11.0), 64^3 2.1 (2.7). Whole-line
+// tiles stay the better on 128^3 in FP32: 3.3 us against 4.4.
 template <typename AT, int S, int VX, int RY, int SIDE>
 __global__ __launch_bounds__((grid3_threads(sizeof(AT), VX, RY))) void k_grid3(G3Args<AT> a) {
     extern __shared__ __align__(16) unsigned char smem[];
