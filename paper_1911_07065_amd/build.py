@@ -17,7 +17,7 @@ HIPCC = os.path.join(ROCM, "bin", "hipcc")
 ARCH = "gfx950"
 
 HIP_SOURCES = ["kernels.hip", "grid2.hip", "grid3.hip", "lband.hip", "driver.hip", "batched.hip", "batched_grid.hip", "batch_driver.hip"]
-HOST_SOURCES = ["host_core.cpp", "poly.cpp"]
+HOST_SOURCES = ["host_core.cpp", "poly.cpp", "grid_shapes.cpp"]
 
 HIP_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",

@@ -204,21 +204,27 @@ struct pp_batch_s {
             for (int r = 0; r < 5; ++r) grid_off(p, r);
     }
     std::vector<int32_t> h_bgx;  // line length of every system's grid (box copy)
+    std::vector<std::pair<int, int>> grids() const {
+        std::vector<std::pair<int, int>> g;
+        for (int s = 0; s < nsys; ++s) g.emplace_back(h_bgx[s], (int)((row_off[s + 1] - row_off[s]) / h_bgx[s]));
+        return g;
+    }
     // The shape's tiles over every system, uploaded (both tile lists in one
     // allocation); off when a region leaves no tile.
     pp_status grid_on(int prec, int R, int ry, int waves, int steps, hipStream_t st) {
         grid_off(prec, R);
-        const int aw = std::min(waves, batch_grid_max_waves(prec == 0 ? 8 : 4, R, ry, true));
+        const int aw = batch_grid_acc_waves(prec, R, ry, waves);
+        const auto gs = grids();
+        if (!batch_grid_fits(prec, R, ry, waves, steps, gs)) return PP_OK;
         std::vector<int4> t;
         size_t first = 0;
         for (int h : {ry * waves, ry * aw}) {
             first = t.size();
             for (int s = 0; s < nsys; ++s) {
-                const int gx = h_bgx[s], gy = (int)((row_off[s + 1] - row_off[s]) / gx);
-                const int tx = gx <= 64 ? gx : 64 - 2 * steps, ty = gy <= h ? gy : h - 2 * steps;
-                if (tx < 1 || ty < 1) return PP_OK;
-                for (int y = 0; y < gy; y += ty)
-                    for (int x = 0; x < gx; x += tx) t.push_back(int4{s, x, y, 0});
+                int tx, ty;
+                batch_grid_tile(gs[s].first, gs[s].second, h, steps, &tx, &ty);
+                for (int y = 0; y < gs[s].second; y += ty)
+                    for (int x = 0; x < gs[s].first; x += tx) t.push_back(int4{s, x, y, 0});
             }
         }
         PP_TRY(dev_alloc(&grid_tiles[prec][R], t.size()));
@@ -564,47 +570,19 @@ pp_status tune_bchain(pp_batch B, int prec, int R, hipStream_t st) {
     }
     c = best;
     c.tuned = 1;
-    return tune_bgrid(B, prec, R, best.us, e0, e1, st);
+    const pp_status g = tune_bgrid(B, prec, R, best.us, e0, e1, st);
+    if (g != PP_OK) c.tuned = 0;
+    return g;
 }
 
 // Times the multi-step kernel's shapes over the whole batch (when it has the
 // box copy and the caller forced no format) and turns on the one with the
-// lowest time per step if that beats `single`, the best single-step launch. The shapes
-// timed are the four best by a model of one step: the launch's memory traffic
-// (the regions read, the tiles written, at a copy's 4.5 TB/s) and 4 us over
-// its steps, then the issue of the regions' operations.
+// lowest time per step if that beats `single`, the best single-step launch. The
+// shapes timed are the four most promising (batch_grid_shapes).
 pp_status tune_bgrid(pp_batch B, int prec, int R, double single, hipEvent_t e0, hipEvent_t e1, hipStream_t st) {
     B->grid_off(prec, R);
     if (B->format_forced || !B->format_ok(2)) return PP_OK;
-    struct Cand {
-        double t;
-        int ry, waves, steps;
-    };
-    std::vector<Cand> all;
-    const double vb = prec == 0 ? 8.0 : 4.0, ops = prec == 0 ? 12.0 : 8.0;
-    for (int ry : {2, 3, 4, 6})
-        for (int waves : {4, 8, 16}) {
-            Cand best{1e30, ry, waves, 0};
-            for (int n = 2; batch_grid_ok(prec, R, ry, waves, n); ++n) {
-                double tiles = 0, pts = 0;
-                bool ok = true;
-                for (int s = 0; s < B->nsys && ok; ++s) {
-                    const int gx = B->h_bgx[s], gy = (int)((B->row_off[s + 1] - B->row_off[s]) / gx), h = ry * waves;
-                    const int tx = gx <= 64 ? gx : 64 - 2 * n, ty = gy <= h ? gy : h - 2 * n;
-                    ok = tx >= 1 && ty >= 1;
-                    if (ok) tiles += (double)((gx + tx - 1) / tx) * ((gy + ty - 1) / ty);
-                    pts += (double)gx * gy;
-                }
-                if (!ok) break;
-                const double region = 64.0 * ry * waves * R;
-                const double mem = (tiles * region + pts * R) * vb / 4.5e6;
-                const double issue = std::max(tiles / 256.0, 1.0) * (region / 64.0) * ops * 4.0 / 4.0 / 2400.0;
-                const double t = (4.0 + mem) / n + 0.12 + issue;
-                if (t < best.t) best = Cand{t, ry, waves, n};
-            }
-            if (best.steps > 0) all.push_back(best);
-        }
-    std::stable_sort(all.begin(), all.end(), [](const Cand &a, const Cand &b) { return a.t < b.t; });
+    const std::vector<BatchGridShape> all = batch_grid_shapes(prec, R, B->grids());
     const BWork &w = B->ws[prec];
     // a program of the most steps: real roots, no accumulator
     BatchProg P;
@@ -612,10 +590,11 @@ pp_status tune_bgrid(pp_batch B, int prec, int R, double single, hipEvent_t e0, 
     PP_TRY(upload(h, &P.steps, st));
     PP_TRY(dev_alloc(&P.segs[prec], B->nsys));
     void *bufs[5] = {w.P(0), w.P(1), w.P(2), w.P(3), w.P(4)};
-    Cand best{single, 0, 0, 0};
+    BatchGridShape best{single, 0, 0, 0};
     for (size_t k = 0; k < all.size() && k < 4; ++k) {
-        const Cand &c = all[k];
+        const BatchGridShape &c = all[k];
         PP_TRY(B->grid_on(prec, R, c.ry, c.waves, c.steps, st));
+        if (B->grid[prec][R].steps == 0) continue;
         std::vector<BatchSeg> sg(B->nsys, BatchSeg{0, c.steps, B_IN, B_OUT, 0, -1, 0, 0});
         HIP_TRY(hipMemcpyAsync(P.segs[prec], sg.data(), sizeof(BatchSeg) * sg.size(), hipMemcpyHostToDevice, st));
         HIP_TRY(hipStreamSynchronize(st));
@@ -632,7 +611,7 @@ pp_status tune_bgrid(pp_batch B, int prec, int R, double single, hipEvent_t e0, 
             HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
             us = std::min(us, 1e3 * ms / 3);
         }
-        if (us / c.steps < best.t) best = Cand{us / c.steps, c.ry, c.waves, c.steps};
+        if (us / c.steps < best.t) best = BatchGridShape{us / c.steps, c.ry, c.waves, c.steps};
     }
     B->grid_off(prec, R);
     if (best.steps == 0) return PP_OK;

@@ -86,14 +86,6 @@ struct BatchGrid {
 struct BatchSeg {
     int first, count, in, out, fin, acc, acc_init, pad;
 };
-// Waves per workgroup at most (0: not built): two vectors of ry R values a
-// lane, three with an accumulator, beside about 60 registers; 16 waves leave
-// a lane 128, 8 waves 256.
-constexpr int batch_grid_max_waves(size_t value_bytes, int R, int ry, bool acc) {
-    const size_t regs = value_bytes / 4 * (size_t)(R * ry) * (acc ? 3 : 2);
-    return regs <= 54 ? 16 : regs <= 96 ? 8 : 0;
-}
-bool batch_grid_ok(int prec, int R, int ry, int waves, int steps);
 // Launch l of L: segment l of every active system (segs: nsys x L); acc: the
 // programs have an accumulator.
 hipError_t launch_bgrid(const BatchSell &S, const BatchGrid &g, bool acc, int prec, int R, const PStep *desc, int K,

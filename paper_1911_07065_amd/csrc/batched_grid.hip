@@ -195,13 +195,6 @@ hipError_t bg_run(const BatchSell &S, const AT *ptab, const BatchGrid &g, bool a
 
 }  // namespace
 
-bool batch_grid_ok(int prec, int R, int ry, int waves, int steps) {
-    const size_t vb = prec == 0 ? 8 : 4;
-    return (prec == 0 || prec == 1) && (R == 1 || R == 2 || R == 4) && (ry == 2 || ry == 3 || ry == 4 || ry == 6) &&
-           waves >= 1 && waves <= batch_grid_max_waves(vb, R, ry, false) && batch_grid_max_waves(vb, R, ry, true) > 0 &&
-           steps >= 2 && steps <= kGrid2MaxSteps && 64 - 2 * steps >= 1;
-}
-
 hipError_t launch_bgrid(const BatchSell &S, const BatchGrid &g, bool acc, int prec, int R, const PStep *desc, int K,
                         const BatchSeg *segs, int L, int l, void *const bufs[5], hipStream_t st) {
     if (!S.bgx || !batch_grid_ok(prec, R, g.ry, g.waves, g.steps)) return hipErrorInvalidValue;

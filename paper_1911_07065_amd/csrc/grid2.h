@@ -7,6 +7,8 @@
 
 #include <cstddef>
 
+#include "grid_shapes.h"
+
 namespace ppg {
 
 // One step of a chain on the vector S the chain is at:
@@ -20,9 +22,6 @@ struct Grid2Step {
     int flags;
 };
 
-// Steps of one launch at most: they travel in the kernel's arguments
-// (1.5 KB in FP64), and past 32 steps the launch itself is below 5 % of the time.
-constexpr int kGrid2MaxSteps = 32;
 constexpr int kGrid2MaxRows = 6;  // rows per wave of the largest built shape
 
 // The matrix as the kernel reads it: rows are the points x + gx y of a gx x
