@@ -173,8 +173,8 @@ pp_status pp_matrix_tune(pp_matrix A, int prec, void *stream, int *variant, int 
  * finishes the step. PP_EINVAL when the copy is absent.
  * Variant 34 (ldsband) holds a band of the input in LDS per workgroup and
  * gathers there; a second launch adds the (at most 8) bands' sums per row
- * in band order and finishes the step. Its copy is built by the tuner or by
- * this call for matrices of at least 4096 rows without a diagonal-format
+ * in band order and finishes the step. Its copy is built by the tuner (which
+ * keeps it if the variant wins) or by this call for matrices of at least 4096 rows without a diagonal-format
  * copy whose vector is at most 8 bands of 128 KB (65536 columns in
  * bfloat16) and whose rows hold at most 127 entries per band; PP_EINVAL
  * elsewhere. */

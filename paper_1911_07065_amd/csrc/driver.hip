@@ -729,7 +729,14 @@ pp_status tune_chain(pp_matrix A, int prec, hipStream_t st) {
     PP_TRY(A->ensure_ws(prec, 0));
     PP_TRY(build_round_plan(A, prec, 8, &A->tileB8[prec], &A->ntileB8[prec], st));
     PP_TRY(build_round_plan(A, prec, 16, &A->tileB16[prec], &A->ntileB16[prec], st));
-    PP_TRY(build_lband(A, prec, st));
+    // the LDS-band copy is only kept when it wins (or was there before:
+    // launches recorded since may read it); no room for it is no failure
+    const bool had_lband = A->lb[prec].nb > 0;
+    const pp_status lb = build_lband(A, prec, st);
+    if (lb == PP_ENOMEM)
+        (void)hipGetLastError();
+    else
+        PP_TRY(lb);
     const Workspace &w = A->ws[prec];
     HIP_TRY(hipMemsetAsync(w.P0, 0, (size_t)w.ldv * elem_size(prec), st));
     HIP_TRY(hipMemsetAsync(w.P1, 0, (size_t)w.ldv * elem_size(prec), st));
@@ -784,6 +791,7 @@ pp_status tune_chain(pp_matrix A, int prec, hipStream_t st) {
         }
     }
     A->variant[prec] = bv;
+    if (bv != CV_LBAND && !had_lband) pp_matrix_s::free_lband(A->lb[prec]);
     A->remap[prec] = br;
     A->persist[prec] = 0;
     double best_all = best;
