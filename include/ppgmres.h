@@ -174,10 +174,10 @@ pp_status pp_matrix_tune(pp_matrix A, int prec, void *stream, int *variant, int 
  * Variant 34 (ldsband) holds a band of the input in LDS per workgroup and
  * gathers there; a second launch adds the (at most 8) bands' sums per row
  * in band order and finishes the step. Its copy is built by the tuner (which
- * keeps it if the variant wins) or by this call for matrices of at least 4096 rows without a diagonal-format
- * copy whose vector is at most 8 bands of 128 KB (65536 columns in
- * bfloat16) and whose rows hold at most 127 entries per band; PP_EINVAL
- * elsewhere. */
+ * keeps it if the variant wins) or by this call for matrices of at least 4096
+ * rows without a diagonal-format copy whose vector is at most 8 bands of
+ * 128 KB (65536 columns in bfloat16) and whose rows hold at most 127 entries
+ * per band; PP_EINVAL elsewhere. */
 pp_status pp_matrix_set_variant(pp_matrix A, int prec, int variant, int remap);
 
 /* The chain-step variant in use for a precision, without tuning: variant
@@ -273,9 +273,12 @@ pp_status pp_matrix_march_shape(pp_matrix A, int prec, int *shape);
  *     PP_EINVAL where it does not apply, for a shape that is not built or
  *     whose region leaves no tile, for bfloat16 vectors, or for a precision
  *     not tuned or set yet. pp_matrix_set_variant and the other fusion
- *     controls turn it off.
+ *     controls turn it off. When new values end a constant stencil, a forced
+ *     2-D shape that is built for per-row coefficients stays; any other gives
+ *     way to the likeliest one for them, or to none (13 points, 3-D).
  *   pp_matrix_grid: shape (host int[4]) = {vx, ry, waves, steps} in use
- *     (steps 0: off; 3-D: by phi(A)v), us the tuned time of one launch (0: forced). */
+ *     (steps 0: off; 3-D: by phi(A)v), us the tuned time of one launch (0: forced,
+ *     or put in place by new values). */
 pp_status pp_matrix_set_grid(pp_matrix A, int prec, int vx, int ry, int waves, int steps);
 pp_status pp_matrix_grid(pp_matrix A, int prec, int *shape, double *us);
 

