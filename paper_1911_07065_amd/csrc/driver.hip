@@ -586,46 +586,6 @@ pp_status build_lband(pp_matrix A, int prec, hipStream_t st) {
     return PP_OK;
 }
 
-// The shapes of the 2-D multi-step kernel worth timing, the most promising
-// first by a model of one step's time fitted to a sweep of all shapes (50^2 to
-// 1024^2; its four best always held one within 3 % of the fastest): 4.6 us a
-// launch over its steps, then per wave of the fullest CU's SIMDs a fixed
-// part and a part per point of a lane.
-void grid2_shapes(const Grid2Mat &m, int prec, std::vector<Grid2Shape> &out) {
-    std::vector<std::pair<double, Grid2Shape>> all;
-    const double fixed = m.nd == 13 ? 0.1 : 0.0, wave = prec == 0 ? 0.05 : 0.025;
-    const double point = m.nd == 13 ? (prec == 0 ? 0.045 : 0.036) : (prec == 0 ? 0.024 : 0.017);
-    for (int vx = 1; vx <= 2; ++vx)
-        for (int ry = 1; ry <= kGrid2MaxRows; ++ry) {
-            if (!grid2_built(m, prec, vx, ry)) continue;
-            const int whole = (m.gy + ry - 1) / ry;  // waves that span the grid's rows
-            for (int waves : {4, 8, 16, whole}) {
-                if (waves > 16 || whole < waves) continue;
-                Grid2Shape s, best;
-                s.vx = vx;
-                s.ry = ry;
-                s.waves = waves;
-                double bt = 1e30;
-                for (int n = 2; n <= kGrid2MaxSteps; ++n) {
-                    int tx, ty;
-                    long tiles;
-                    if (!grid2_tiles(m, s, n, &tx, &ty, &tiles)) break;
-                    const double per_simd = (double)((tiles + 255) / 256) * std::max(1.0, waves / 4.0);
-                    const double t = 4.6 / n + fixed + per_simd * (wave + point * ry * vx);
-                    if (t < bt) {
-                        bt = t;
-                        best = s;
-                        best.steps = n;
-                    }
-                }
-                if (best.steps > 0) all.emplace_back(bt, best);
-            }
-        }
-    std::stable_sort(all.begin(), all.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
-    out.clear();
-    for (const auto &a : all) out.push_back(a.second);
-}
-
 // Time the 2-D multi-step kernel's likeliest shapes and keep the one with the
 // lowest time per step when it beats `single`, a step's time in a launch of
 // its own.
@@ -634,8 +594,7 @@ pp_status tune_grid2(pp_matrix A, int prec, double single, hipEvent_t e0, hipEve
     if (A->g2_nd == 0 || prec == PP_BF16S) return PP_OK;
     const Workspace &w = A->ws[prec];
     const Grid2Mat m = A->grid2();
-    std::vector<Grid2Shape> shapes;
-    grid2_shapes(m, prec, shapes);
+    const std::vector<Grid2Shape> shapes = grid2_shapes(m.form(), prec);
     Grid2Step<double> u[kGrid2MaxSteps];
     for (auto &t : u) t = Grid2Step<double>{1.0, 0.0, 0.0, 0.0, 0.0, 0};
     double best = single;
@@ -2326,8 +2285,7 @@ pp_status refresh_values(pp_matrix A, const double *val, hipStream_t st) {
                 if (A->g2[p].steps == 0 || was_const == (A->g2_pint >= 0)) continue;
                 const bool forced = A->g2_us[p] == 0.0;
                 if (forced && grid2_built(A->grid2(), p, A->g2[p].vx, A->g2[p].ry)) continue;
-                std::vector<Grid2Shape> shapes;
-                grid2_shapes(A->grid2(), p, shapes);
+                const std::vector<Grid2Shape> shapes = grid2_shapes(A->grid2().form(), p);
                 A->grid_off(p);
                 if (!shapes.empty()) A->g2[p] = shapes[0];
             }
@@ -2768,7 +2726,7 @@ pp_status pp_matrix_set_grid(pp_matrix A, int prec, int vx, int ry, int waves, i
     long tiles;
     const bool ok = A->box_nd == 7 ? A->has_grid3() && grid3_built(A->grid3(), prec, s) && grid3_fit(A->grid3(), s)
                                    : A->g2_nd != 0 && grid2_built(A->grid2(), prec, vx, ry) &&
-                                         grid2_tiles(A->grid2(), s, steps, &tx, &ty, &tiles);
+                                         grid2_tiles(A->grid2().form(), s, steps, &tx, &ty, &tiles);
     if (steps > 0 && !ok) {
         set_error("pp_matrix_set_grid: needs a 5- or 13-point stencil on a 2-D grid or a 7-point one on a 3-D grid "
                   "(7 and 13 points: constant coefficients), FP64 or FP32 vectors, and a built shape whose region leaves a tile");

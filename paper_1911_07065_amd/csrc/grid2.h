@@ -22,8 +22,6 @@ struct Grid2Step {
     int flags;
 };
 
-constexpr int kGrid2MaxRows = 6;  // rows per wave of the largest built shape
-
 // The matrix as the kernel reads it: rows are the points x + gx y of a gx x
 // gy grid, nd = 5 or 13 diagonals (the stencils of Grid2), no stored entry
 // joins grid lines' ends. coef64/32: every row is these nd coefficients
@@ -36,21 +34,14 @@ struct Grid2Mat {
     const double *dval64 = nullptr;
     const float *dval32 = nullptr;
     bool constant() const { return coef64 != nullptr; }
-    int rho() const { return nd == 13 ? 2 : 1; }
+    int rho() const { return form().rho(); }
+    Grid2Form form() const { return Grid2Form{gx, gy, nd, constant()}; }
 };
 
-// How a launch is split: vx adjacent columns per lane and ry rows per wave,
-// `waves` waves per workgroup: a region of 64 vx x waves ry points.
-struct Grid2Shape {
-    int vx = 0, ry = 0, waves = 0;
-    int steps = 0;  // steps per launch
-    int tz = 0;     // planes per chunk (3-D grids)
-};
-
-// The (vx, ry) pairs that are built for this matrix and precision (0: FP64, 1: FP32).
-bool grid2_built(const Grid2Mat &m, int prec, int vx, int ry);
-// Tile sides and count of a launch of n steps; false when the region leaves no tile.
-bool grid2_tiles(const Grid2Mat &m, const Grid2Shape &s, int n, int *tx, int *ty, long *tiles);
+// The shape is built for this matrix and precision (0: FP64, 1: FP32).
+inline bool grid2_built(const Grid2Mat &m, int prec, int vx, int ry) {
+    return (m.constant() || m.dval64) && grid2_built(m.form(), prec, vx, ry);
+}
 
 struct Grid2Ptrs {
     const void *in;

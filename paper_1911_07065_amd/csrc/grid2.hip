@@ -150,7 +150,7 @@ hipError_t g2_run(const Grid2Mat &m, const AT *coef, const AT *dval, const Grid2
                   int remap, hipStream_t st) {
     G2Args<AT> a;
     long tiles = 0;
-    if (p.n < 1 || p.n > kGrid2MaxSteps || !grid2_tiles(m, s, p.n, &a.tx, &a.ty, &tiles) || tiles >= (1L << 31) ||
+    if (p.n < 1 || p.n > kGrid2MaxSteps || !grid2_tiles(m.form(), s, p.n, &a.tx, &a.ty, &tiles) || tiles >= (1L << 31) ||
         (m.constant() ? !coef : !dval))
         return hipErrorInvalidValue;
     a.in = (const AT *)p.in;
@@ -178,22 +178,6 @@ hipError_t g2_run(const Grid2Mat &m, const AT *coef, const AT *dval, const Grid2
 }
 
 }  // namespace
-
-bool grid2_built(const Grid2Mat &m, int prec, int vx, int ry) {
-    if ((prec != 0 && prec != 1) || !((m.nd == 5 && (m.constant() || m.dval64)) || (m.nd == 13 && m.constant()))) return false;
-    if (vx * ry > 4 && !m.constant()) return false;
-    return (vx == 1 && (ry == 2 || ry == 3 || ry == 4 || ry == 6)) || (vx == 2 && (ry == 2 || ry == 3 || ry == 4));
-}
-
-bool grid2_tiles(const Grid2Mat &m, const Grid2Shape &s, int n, int *tx, int *ty, long *tiles) {
-    if (s.vx < 1 || s.ry < 1 || s.waves < 1 || s.waves > 16 || m.gx < 2 || m.gy < 1) return false;
-    const int w = 64 * s.vx, h = s.waves * s.ry, halo = 2 * m.rho() * n;
-    *tx = m.gx <= w ? m.gx : w - halo;
-    *ty = m.gy <= h ? m.gy : h - halo;
-    if (*tx < 1 || *ty < 1) return false;
-    *tiles = (long)((m.gx + *tx - 1) / *tx) * ((m.gy + *ty - 1) / *ty);
-    return true;
-}
 
 hipError_t launch_chain_grid2(const Grid2Mat &m, int prec, const Grid2Shape &s, const Grid2Ptrs &p, int remap,
                               hipStream_t st) {

@@ -42,8 +42,31 @@ static long batch_case(const std::vector<std::pair<int, int>> &grids) {
     return n;
 }
 
+// Every shape offered for a 2-D grid is built, leaves a tile and is offered once.
+static long grid2_case(const Grid2Form &m) {
+    long n = 0;
+    for (int prec = 0; prec < 2; ++prec) {
+        const std::vector<Grid2Shape> all = grid2_shapes(m, prec);
+        for (size_t i = 0; i < all.size(); ++i) {
+            int tx, ty;
+            long tiles;
+            CHECK(grid2_built(m, prec, all[i].vx, all[i].ry) && grid2_tiles(m, all[i], all[i].steps, &tx, &ty, &tiles),
+                  "%d x %d", m.gx, m.gy);
+            for (size_t k = 0; k < i; ++k)
+                CHECK(all[i].vx != all[k].vx || all[i].ry != all[k].ry || all[i].waves != all[k].waves,
+                      "%d x %d: shape %d x %d x %d twice", m.gx, m.gy, all[i].vx, all[i].ry, all[i].waves);
+            ++n;
+        }
+    }
+    return n;
+}
+
 int main() {
     long n = 0;
+    for (int gy = 3; gy <= 130; ++gy)
+        for (int gx : {3, 50, 64, 200, 1024})
+            for (int form = 0; form < 3; ++form)
+                if (form < 2 || (gx >= 5 && gy >= 5)) n += grid2_case(Grid2Form{gx, gy, form == 2 ? 13 : 5, form != 1});
     for (int count : {1, 8, 16, 32, 48, 96, 128, 256})
         for (int side = 3; side <= 260; ++side) n += batch_case({(size_t)count, {side, side}});
     std::mt19937 rng(5);
