@@ -1349,7 +1349,7 @@ void program_bytes(pp_matrix A, pp_poly poly, int kind, int prec, int64_t &bytes
     plan_program(A, prog, prec, plan);
     for (const Planned &L : plan) {
         const Step &s = prog[L.i], &t = prog[L.i + L.g - 1];
-        if (L.kind == 3) {
+        if (L.kind == 3 && !(A->box_nd == 7 && L.g == 1)) {  // a 3-D program's single steps run as such
             // the coefficients (or the diagonal format's values), the input,
             // the accumulator or the final vector, the output: each once
             const int64_t slots = A->box_nd == 7 || A->g2_pint >= 0 ? 1 : ((int64_t)A->n + 255) / 256 * 256;

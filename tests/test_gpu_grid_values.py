@@ -1,5 +1,6 @@
 """The 2-D multi-step shape in use follows new values: it stays while its kernel
-does, and a shape whose kernel changed never reports the old one's time."""
+does, and a shape whose kernel changed never reports the old one's time. And
+the byte count of a 3-D program whose launches are of different lengths."""
 
 import numpy as np
 import pytest
@@ -72,3 +73,24 @@ def test_tuned_shape_reports_no_time_of_another_kernel(pp):
     M.set_values(dev(vals))
     assert M.grid("fp64")[1] == 0.0
     _right(pp, M, csr, vals, (150, 150))
+
+
+@pytest.mark.parametrize("variant", ["sell64", "diapv"])
+def test_box_chain_bytes_count_single_steps_as_such(pp, variant):
+    # a 3-D program's launches of one step run the single-step variant: they
+    # read its matrix data, not the interior row's coefficients alone
+    csr = convdiff3d_box(40, 30, 20, 4.0, 2.0, 1.0)
+    M = pp.Matrix.from_csr(csr)
+    names = [pp.chain_variant_name(k) for k in range(pp.N_CHAIN_VARIANTS)]
+    one = pp.poly_from_roots([3.0], keep_order=True)
+    mixed = pp.poly_from_roots([3.0, 5 + 1j, 5 - 1j], keep_order=True)
+    for prec, size in (("fp64", 8), ("fp32", 4)):
+        M.set_variant(prec, names.index(variant), 1)
+        single = pp.chain_bytes(one, M, "phi", prec)  # matrix data; input, final vector, output
+        matrix = single[0] - 3 * csr.n * size
+        M.set_grid(prec, 1, 2, 8, 2)
+        say("chain bytes, single steps", variant, prec)
+        assert pp.chain_bytes(one, M, "phi", prec) == single
+        # the real root alone (input, output), then the pair in one launch
+        # (input, final vector, output, seven coefficients)
+        assert pp.chain_bytes(mixed, M, "phi", prec) == (matrix + 5 * csr.n * size + 7 * size, 2)
