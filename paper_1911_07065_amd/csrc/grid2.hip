@@ -121,8 +121,10 @@ hipError_t g2_launch(const G2Args<AT> &a, const Grid2Shape &s, hipStream_t st) {
 // The built shapes (grid2_built): one column of 2, 3, 4 or 6 rows a lane, or
 // two of 2, 3 or 4. One row a wave pays the barrier for too little work and
 // 12 or 16 points a lane (8 waves, their registers) gain nothing: at 1024^2 in FP64
-// 1.41 us a step with 2 x 4, 1.49 with 2 x 8. Per-row coefficients stay in
-// registers, 5 a point, so those stop at 4 points a lane.
+// 1.41 us a step with 2 x 4, 1.49 with 2 x 8 (2 x 4 in FP64 spills 4 vector
+// registers of its 128, with 13 points 18; the tuner times it like the
+// others). Per-row coefficients stay in registers, 5 a point, so those stop
+// at 4 points a lane.
 template <typename AT, int ND, bool VAR>
 hipError_t g2_shape(const G2Args<AT> &a, const Grid2Shape &s, hipStream_t st) {
     switch (s.vx * 10 + s.ry) {

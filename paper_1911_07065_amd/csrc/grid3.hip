@@ -97,8 +97,10 @@ struct March3 {
     }
     // Step l, read from the kernel's arguments where it is used: with an
     // accumulator in FP64, three steps kept in scalar registers are spilled to
-    // lanes and read back value by value (201 x 150 x 97 p 8.6 us a step, 8.5
-    // so; 50^3 2.75 and 2.64). Elsewhere they fit and the reads only cost.
+    // lanes and read back value by value (49 registers, 4 to 13 so; 201 x 150
+    // x 97 p 8.6 us a step, 8.5 so; 50^3 2.75 and 2.64). FP32 with an
+    // accumulator spills 18 to 35 with three steps, but ran no faster with
+    // the reads, and forms without one, which hardly spill, 1 % slower.
     static constexpr bool kReread = SIDE == ACC && sizeof(AT) == 8;
     static __device__ __forceinline__ Grid2Step<AT> step_args(int l) {
         typedef __attribute__((address_space(4))) const char *Args;
@@ -232,7 +234,8 @@ struct March3 {
 // chain kernels: FP64 201 x 150 x 97 phi 6.8 us (14.7), p 8.5 us (18.3), 256 x
 // 256 x 200 18.2 (33.8) and 36.9 (70.1), 64^3 phi 2.5 (2.7), 30^3 2.1 (3.0);
 // FP32 201 x 150 x 97 5.2 (8.1) and 6.5 (11.0), 64^3 2.1 (2.7). Whole-line
-// tiles stay the better on 128^3 in FP32: 3.3 us against 4.4.
+// tiles stay the better on 128^3 in FP32: phi 3.4 us against 4.5, p 4.5
+// against 5.6.
 template <typename AT, int S, int VX, int RY, int SIDE>
 __global__ __launch_bounds__((grid3_threads(sizeof(AT), VX, RY))) void k_grid3(G3Args<AT> a) {
     extern __shared__ __align__(16) unsigned char smem[];

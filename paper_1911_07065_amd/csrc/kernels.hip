@@ -3134,7 +3134,7 @@ hipError_t launch_dots(int prec, int n, const void *V, long ldv, int ncols, cons
     if (g == 0 || ncols == 0) return hipSuccess;
     // fewer than four workgroups per CU: one per eight columns as well, so
     // that a basis' chunks are not one chain of loads and reductions (adjoint
-    // pair of solves on 512^2 in FP64 8.32 -> 8.20 ms, on 200^2 2.74 -> 2.69)
+    // pair of solves on 512^2 in FP64 8.31 -> 8.11 ms, on 200^2 2.70 -> 2.63)
     const dim3 grid(g, g < 1024 ? (ncols + 7) / 8 : 1);
     switch (prec) {
         case 0:
